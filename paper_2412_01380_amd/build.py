@@ -10,7 +10,7 @@ ROOT = os.path.dirname(HERE)
 CSRC = os.path.join(HERE, "csrc")
 LIBDIR = os.path.join(HERE, "lib")
 LIBPATH = os.path.join(LIBDIR, "libdip.so")
-SOURCES = ["dip_api.hip", "dip_select.hip", "dip_gemv.hip", "dip_batched.hip", "dip_tier.hip"]
+SOURCES = ["dip_api.hip", "dip_select.hip", "dip_gemv.hip", "dip_rows.hip", "dip_stack.hip", "dip_batched.hip", "dip_tier.hip"]
 # dip_fused.hip is compiled once per (segments, weight type): six objects built in parallel
 FUSED_VARIANTS = [(nseg, dtype) for nseg in (1, 2) for dtype in (0, 1, 2)]
 

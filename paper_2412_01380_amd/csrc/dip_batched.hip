@@ -554,7 +554,7 @@ __global__ void breduce_kernel(BatchedReduceParams p) {
     const int width = p.glu ? p.n_out / 2 : p.n_out;
     if (j >= width) return;
     const size_t gstride = (size_t)p.batch * (size_t)p.n_out;
-    const float* src = p.partial + (size_t)b * (size_t)p.n_out + j;
+    const float* src = p.partial + blockIdx.z * p.partial_layer_stride + (size_t)b * (size_t)p.n_out + j;
     float s0 = 0.f, s1 = 0.f;
     // (loads past the last share re-read it and are dropped: a load under a branch would be
     //  waited for where the branch ends, one round trip each)
@@ -572,7 +572,7 @@ __global__ void breduce_kernel(BatchedReduceParams p) {
         for (int i = 0; i < kInFlight; ++i)
             if (g0 + i < p.shares) { s0 += a8[i]; s1 += b8[i]; }
     }
-    p.out[(size_t)b * p.out_stride + j] = p.glu ? s0 * (s1 / (1.0f + expf(-s1))) : s0;
+    p.out[blockIdx.z * p.out_layer_stride + (size_t)b * p.out_stride + j] = p.glu ? s0 * (s1 / (1.0f + expf(-s1))) : s0;
 }
 
 template <int DT>
@@ -637,9 +637,9 @@ hipError_t launch_batched_gemv(const BatchedGemvParams& p, int shares, bool mc, 
     return hipErrorInvalidValue;
 }
 
-hipError_t launch_batched_reduce(const BatchedReduceParams& p, hipStream_t stream) {
+hipError_t launch_batched_reduce(const BatchedReduceParams& p, int layers, hipStream_t stream) {
     const int width = p.glu ? p.n_out / 2 : p.n_out;
-    hipLaunchKernelGGL(breduce_kernel, dim3((width + 255) / 256, p.batch), dim3(256), 0, stream, p);
+    hipLaunchKernelGGL(breduce_kernel, dim3((width + 255) / 256, p.batch, layers), dim3(256), 0, stream, p);
     return hipGetLastError();
 }
 

@@ -12,18 +12,9 @@
 // ballot over one slot is two words of the mask and (slot, wavefront) tiles in ascending
 // order are the features in index order (lowest index wins ties; ascending list).
 //
-// Cache-aware scores without a division per key.  Eq. 10 of Sec. 5.2 is s = fl(p / M) with
-// p = |v| for resident columns, fl(|v| * gamma) otherwise, and M = ||v||_inf.  q -> fl(q / M)
-// is monotone, so the k-th largest score is T_s = fl(T_p / M) with T_p the k-th largest p, and
-//     { s > T_s }  = { p >= P_hi },  P_hi = the smallest float with fl(P_hi / M) >  T_s
-//     { s == T_s } = { P_lo <= p < P_hi },  P_lo = the smallest float with fl(P_lo / M) >= T_s.
-// The selection therefore runs on the bit patterns of p, and only P_lo and P_hi need
-// divisions: 64 candidates around T_p, one per lane, settle them in one step (a bisection
-// over all floats covers the case that the window is too small, e.g. denormal scores).  The
-// selected set is then exactly the top-K of the rounded scores with lowest-index ties -- the
-// set the stand-alone selection kernel and the oracle produce from the emitted s.
+// (The selection itself: dip_head_device.h.)
 #include "dip_gemv_device.h"
-#include "dip_select_device.h"
+#include "dip_head_device.h"
 
 namespace dip {
 namespace {
@@ -32,105 +23,6 @@ using namespace sel;
 using namespace gemv;
 
 constexpr int kFusedWaves = kSelThreads / 64;   // 16
-
-struct HeadShared {
-    uint32_t hist[kBinsA + kBinsB + kBinsC];
-    uint32_t cw[kMaxWords];          // residency words used for scoring
-    uint32_t tile[2][kMaxTiles];
-    uint32_t wave_tot[2][kWaves];
-    float wave_max[kWaves];
-    uint32_t bcast[4];
-    uint32_t cand[kNearCand];        // keys of the threshold bin
-    uint32_t ncand;
-};
-constexpr int kHeadHistWords = kBinsA + kBinsB + kBinsC;
-
-// Exclusive running sums of the per-tile counts over the tiles in index order: lane j of each
-// wavefront passes the count of the wavefront's tile in slot j and gets the sum over the tiles
-// before it; `total` is the sum over all tiles.
-template <int ITEMS>
-__device__ __forceinline__ uint32_t tile_scan(uint32_t cnt, HeadShared& sh, int& phase, uint32_t& total) {
-    const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
-    constexpr int ntiles = ITEMS * kWaves;
-    if (lane < ITEMS) sh.tile[0][lane * kWaves + wave] = cnt;
-    __syncthreads();
-    const uint32_t t = tid < ntiles ? sh.tile[0][tid] : 0u;
-    const uint32_t ex = block_excl_scan(t, sh, phase);
-    if (tid < ntiles) sh.tile[0][tid] = ex;
-    if (tid == ntiles - 1) sh.bcast[3] = ex + t;
-    __syncthreads();
-    total = sh.bcast[3];
-    return lane < ITEMS ? sh.tile[0][lane * kWaves + wave] : 0u;
-}
-
-// Smallest float bit pattern c in [lo, hi] with pred(fl(c / M)) true, where pred is monotone
-// (false ... false true ... true) and true at hi.  Every lane runs the same bisection.
-template <bool STRICT>
-__device__ __forceinline__ uint32_t bisect_quotient(uint32_t lo, uint32_t hi, float M, float Ts) {
-    while (lo < hi) {
-        const uint32_t mid = lo + ((hi - lo) >> 1);
-        const float q = __fdiv_rn(__uint_as_float(mid), M);
-        const bool ok = STRICT ? (q > Ts) : (q >= Ts);
-        if (ok) hi = mid; else lo = mid + 1u;
-    }
-    return lo;
-}
-
-// The keys that tie with the k-th largest score, and those above it (Eq. 10 without a division
-// per key, see the head of this file): Tk is the k-th largest key (bits(p) << 1), M = ||v||_inf.
-// Leaves K_lo, K_hi alone when M is 0 (all scores are 0).
-__device__ __forceinline__ void score_window(uint32_t Tk, float M, int lane, uint32_t& K_lo, uint32_t& K_hi) {
-    if (!(M > 0.f)) return;
-    const uint32_t Tb = Tk >> 1;
-    const float Ts = __fdiv_rn(__uint_as_float(Tb), M);
-    constexpr uint32_t kInf = 0x7f800000u;
-    const int64_t cand = (int64_t)Tb + lane - 31;
-    const uint32_t cb = cand < 0 ? 0u : (cand > (int64_t)kInf ? kInf : (uint32_t)cand);
-    const float qc = __fdiv_rn(__uint_as_float(cb), M);
-    const uint64_t ge = __ballot(qc >= Ts), gt = __ballot(qc > Ts);   // lane 31 is T_p: in ge
-    const uint32_t c0 = (uint32_t)__builtin_amdgcn_readfirstlane((int)cb);
-    uint32_t Plo, Phi;
-    if ((ge & 1ull) && c0 > 0u) {
-        Plo = bisect_quotient<false>(0u, c0, M, Ts);
-    } else {
-        // (ge is never empty for finite inputs: lane 31 holds T_p itself)
-        Plo = ge ? (uint32_t)__builtin_amdgcn_readlane((int)cb, __builtin_ctzll(ge)) : Tb;
-    }
-    if (gt == 0ull) {
-        Phi = bisect_quotient<true>(Tb + 1u, kInf, M, Ts);
-    } else {
-        Phi = (uint32_t)__builtin_amdgcn_readlane((int)cb, __builtin_ctzll(gt));
-    }
-    K_lo = Plo << 1;
-    K_hi = Phi << 1;
-}
-
-// Per-tile counts of the keys in [K_lo, K_hi) (low 16 bits) and >= K_hi (high 16 bits), their
-// exclusive prefix over the tiles in index order (lane j of each wavefront returns the prefix
-// of the wavefront's tile in slot j), and the totals.
-template <int ITEMS>
-__device__ __forceinline__ uint32_t tile_prefix_window(const uint32_t (&key)[ITEMS], uint32_t K_lo, uint32_t K_hi,
-                                                       HeadShared& sh, int& phase, uint32_t& totals) {
-    const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
-    constexpr int ntiles = ITEMS * kWaves;
-    uint32_t mine = 0;
-#pragma unroll
-    for (int j = 0; j < ITEMS; ++j) {
-        const uint32_t ce = (uint32_t)__popcll(__ballot(key[j] >= K_lo && key[j] < K_hi));
-        const uint32_t cg = (uint32_t)__popcll(__ballot(key[j] >= K_hi));
-        mine = lane == j ? (ce | (cg << 16)) : mine;
-    }
-    __syncthreads();       // (the table may still be read by a slower wavefront)
-    if (lane < ITEMS) sh.tile[0][lane * kWaves + wave] = mine;
-    __syncthreads();
-    const uint32_t t = tid < ntiles ? sh.tile[0][tid] : 0u;
-    const uint32_t ex = block_excl_scan(t, sh, phase);
-    if (tid < ntiles) sh.tile[0][tid] = ex;
-    if (tid == kSelThreads - 1) sh.bcast[3] = ex + t;
-    __syncthreads();
-    totals = sh.bcast[3];
-    return lane < ITEMS ? sh.tile[0][lane * kWaves + wave] : 0u;
-}
 
 // One slot of the selection `key >= T` into the workgroup's share of the list; slots whose
 // bit of `active` is clear cost one scalar test.  (A template recursion rather than a loop:
@@ -151,37 +43,6 @@ struct ListGe {
             }
         }
         if constexpr (J + 1 < ITEMS) ListGe<J + 1, ITEMS>::run(key, v, T, pre, active, kb, ke, l_idx, l_val);
-    }
-};
-
-// Mask words of the selection, slot by slot (a template recursion: the lane numbers are constants).
-template <int J, int ITEMS>
-struct MaskWords {
-    __device__ static __forceinline__ void run(const uint32_t (&key)[ITEMS], uint32_t K_lo, uint32_t K_hi, bool fast,
-                                               uint32_t take, uint32_t eq_seen, int next, int G, int& my_word) {
-        // `next`: the next slot of this workgroup (g, g + G, ...; uniform, and no division)
-        if (J == next) {
-            slot(key, K_lo, K_hi, fast, take, eq_seen, my_word);
-            next += G;
-        }
-        if constexpr (J + 1 < ITEMS) MaskWords<J + 1, ITEMS>::run(key, K_lo, K_hi, fast, take, eq_seen, next, G, my_word);
-    }
-    __device__ static __forceinline__ void slot(const uint32_t (&key)[ITEMS], uint32_t K_lo, uint32_t K_hi, bool fast,
-                                                uint32_t take, uint32_t eq_seen, int& my_word) {
-        bool mine;
-        if (fast) {
-            mine = key[J] >= K_lo;
-        } else {
-            // ties at the threshold: the `take` lowest indices among them are selected
-            mine = key[J] >= K_hi;
-            const bool tie = key[J] >= K_lo && !mine;
-            const uint64_t be = __ballot(tie);
-            const uint32_t eq_before = (uint32_t)__builtin_amdgcn_readlane((int)eq_seen, J) & 0xffffu;
-            mine = mine || (tie && eq_before + lanes_below(be) < take);
-        }
-        const uint64_t bs = __ballot(mine);
-        write_lane<(2 * J) & 63>(my_word, (uint32_t)bs);
-        write_lane<(2 * J + 1) & 63>(my_word, (uint32_t)(bs >> 32));
     }
 };
 
@@ -224,57 +85,9 @@ __global__ __launch_bounds__(kSelThreads) void fused_kernel(FusedParams fp) {
     uint32_t key[ITEMS];
     const int mine_n = q.n > tid ? (q.n - tid - 1) / kSelThreads + 1 : 0;
     const uint32_t valid = mine_n >= 32 ? 0xffffffffu : (1u << mine_n) - 1u;
-    {
-        const float* vp = q.v + tid;
-        const int full = q.n >> 10;     // slots that lie inside the vector entirely (wave-uniform)
-#pragma unroll
-        for (int j = 0; j < ITEMS; ++j) {
-            if (j < full) {
-                v[j] = vp[j * kSelThreads];
-            } else {
-                const uint32_t i = (uint32_t)(j * kSelThreads + tid);
-                v[j] = 0.f;
-                if (i < (uint32_t)q.n) v[j] = q.v[i & (DIP_MAX_N - 1)];
-            }
-        }
-    }
-    static_assert(kHeadHistWords % (2 * kSelThreads) == 0, "the histograms are cleared in 8-byte pieces");
-#pragma unroll
-    for (int b = 0; b < kHeadHistWords / (2 * kSelThreads); ++b)
-        reinterpret_cast<uint2*>(hs.hist)[b * kSelThreads + tid] = make_uint2(0u, 0u);
-    hs.cw[tid] = (q.score_bits && tid < nwords) ? q.score_bits[tid] : 0u;
-    {
-        // ||v||_inf: the denominator of Eq. 10, and the anchor of the selection's histogram
-        float vmax = 0.f;
-#pragma unroll
-        for (int j = 0; j < ITEMS; ++j) vmax = fmaxf(vmax, fabsf(v[j]));
-        // (fmaxf drops a NaN operand: non-finite inputs leave M finite or infinite, never NaN)
-        vmax = wave_max_nonneg(vmax);
-        if (lane == 0) hs.wave_max[wave] = vmax;
-    }
-    __syncthreads();
-    static_assert(kWaves == 16, "one wavefront maximum per lane of a 16-lane row");
-    const float M = row_max_nonneg(hs.wave_max[lane & (kWaves - 1)]);
-
-    // p = |v| for resident columns, fl(|v| * gamma) for the others (plain DIP: p = |v|); p <= M
-    if (q.score_bits) {
-#pragma unroll
-        for (int j = 0; j < ITEMS; ++j) {
-            const float a = fabsf(v[j]);
-            const uint32_t c = (hs.cw[j * (kSelThreads / 32) + (tid >> 5)] >> (tid & 31)) & 1u;
-            key[j] = __float_as_uint(c ? a : __fmul_rn(a, q.gamma)) << 1;
-        }
-    } else {
-#pragma unroll
-        for (int j = 0; j < ITEMS; ++j) key[j] = __float_as_uint(fabsf(v[j])) << 1;
-    }
-
-    uint32_t Tk, need;
-    block_select_largest_near_max<ITEMS>(key, __float_as_uint(M) << 1, (uint32_t)p.k, hs, phase, Tk, need);
-
-    // keys in [K_lo, K_hi) tie at the k-th largest score, keys >= K_hi lie above it
-    uint32_t K_lo = Tk, K_hi = Tk + 1u;
-    if (q.score_bits) score_window(Tk, M, lane, K_lo, K_hi);
+    float M;
+    uint32_t K_lo, K_hi;    // keys in [K_lo, K_hi) tie at the k-th largest score, keys >= K_hi lie above it
+    head_threshold<ITEMS>(q.v, q.n, (uint32_t)p.k, q.score_bits, q.gamma, hs, phase, v, key, M, K_lo, K_hi);
 
     // ---- this workgroup's share of the list ---------------------------------------------------
     // Counts of the keys >= K_lo per (slot, wavefront) tile and their running sums in index
@@ -411,105 +224,6 @@ hipError_t launch_lpr(const FusedParams& fp, const GemvShape& s, hipStream_t str
 }
 
 
-#if DIP_FUSED_NSEG == 1 && DIP_FUSED_DTYPE == 0
-// ---- row selections of a small batch --------------------------------------------------------
-// One workgroup per row runs the head above on that row -- keys without a division, one
-// histogram pass, the exact-tie window -- and leaves the row's mask words (and the bit pattern
-// of max |v|, which the matrix-core product scales by).  No lists: the union kernel builds
-// them from the masks of all rows.
-struct RowsShared {
-    HeadShared head;
-    uint32_t mwords[kMaxWords];
-    uint32_t wave_cnt[kWaves];
-};
-
-template <int ITEMS>
-__global__ __launch_bounds__(kSelThreads) void rows_select_kernel(SelectParams p) {
-    __shared__ __align__(16) RowsShared sh;
-    HeadShared& hs = sh.head;
-    const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
-    const int nwords = (p.n + 31) >> 5;
-    const float* vrow = p.v + (size_t)blockIdx.x * p.v_row_stride;
-    uint32_t* mrow = p.mask_out + (size_t)blockIdx.x * p.words_row_stride;
-    int phase = 0;
-
-    float v[ITEMS];
-    uint32_t key[ITEMS];
-    {
-        const float* vp = vrow + tid;
-        const int full = p.n >> 10;     // slots that lie inside the vector entirely (wave-uniform)
-#pragma unroll
-        for (int j = 0; j < ITEMS; ++j) {
-            if (j < full) {
-                v[j] = vp[j * kSelThreads];
-            } else {
-                const uint32_t i = (uint32_t)(j * kSelThreads + tid);
-                v[j] = 0.f;
-                if (i < (uint32_t)p.n) v[j] = vrow[i & (DIP_MAX_N - 1)];
-            }
-        }
-    }
-#pragma unroll
-    for (int b = 0; b < kHeadHistWords / (2 * kSelThreads); ++b)
-        reinterpret_cast<uint2*>(hs.hist)[b * kSelThreads + tid] = make_uint2(0u, 0u);
-    hs.cw[tid] = (p.score_bits && tid < nwords) ? p.score_bits[tid] : 0u;
-    {
-        float vmax = 0.f;
-#pragma unroll
-        for (int j = 0; j < ITEMS; ++j) vmax = fmaxf(vmax, fabsf(v[j]));
-        vmax = wave_max_nonneg(vmax);
-        if (lane == 0) hs.wave_max[wave] = vmax;
-    }
-    __syncthreads();
-    const float M = row_max_nonneg(hs.wave_max[lane & (kWaves - 1)]);
-    if (p.rowmax_out && tid == 0) p.rowmax_out[blockIdx.x] = __float_as_uint(M);
-    if (p.score_bits) {
-#pragma unroll
-        for (int j = 0; j < ITEMS; ++j) {
-            const float a = fabsf(v[j]);
-            const uint32_t c = (hs.cw[j * (kSelThreads / 32) + (tid >> 5)] >> (tid & 31)) & 1u;
-            key[j] = __float_as_uint(c ? a : __fmul_rn(a, p.gamma)) << 1;
-        }
-    } else {
-#pragma unroll
-        for (int j = 0; j < ITEMS; ++j) key[j] = __float_as_uint(fabsf(v[j])) << 1;
-    }
-    uint32_t Tk, need;
-    block_select_largest_near_max<ITEMS>(key, __float_as_uint(M) << 1, (uint32_t)p.k, hs, phase, Tk, need);
-    uint32_t K_lo = Tk, K_hi = Tk + 1u;
-    if (p.score_bits) score_window(Tk, M, lane, K_lo, K_hi);
-
-    // how many keys reach K_lo: exactly k means no tie is split at the threshold
-    uint32_t n_wave = 0u;
-#pragma unroll
-    for (int j = 0; j < ITEMS; ++j) n_wave += (uint32_t)__popcll(__ballot(key[j] >= K_lo));
-    if (lane == 0) sh.wave_cnt[wave] = n_wave;
-    __syncthreads();
-    uint32_t n_ge = 0u;
-#pragma unroll
-    for (int w = 0; w < kWaves; ++w) n_ge += sh.wave_cnt[w];
-    const bool fast = n_ge == (uint32_t)p.k;
-    uint32_t take = 0u, eq_seen = 0u;
-    if (!fast) {
-        uint32_t totals;
-        const int pre = (int)tile_prefix_window<ITEMS>(key, K_lo, K_hi, hs, phase, totals);
-        take = (uint32_t)p.k > (totals >> 16) ? (uint32_t)p.k - (totals >> 16) : 0u;
-        eq_seen = (uint32_t)pre;
-    }
-    int my_word = 0;
-    MaskWords<0, ITEMS>::run(key, K_lo, K_hi, fast, take, eq_seen, 0, 1, my_word);
-    if (lane < 2 * ITEMS)
-        sh.mwords[((lane >> 1) * (kSelThreads / 32) + wave * 2 + (lane & 1)) & (kMaxWords - 1)] = (uint32_t)my_word;
-    __syncthreads();
-    if (tid < nwords) mrow[tid] = sh.mwords[tid];
-}
-
-template <int ITEMS>
-hipError_t launch_rows_items(const SelectParams& p, hipStream_t stream, int pk) {
-    return launch_timed(rows_select_kernel<ITEMS>, dim3(p.rows), dim3(kSelThreads), stream, pk, p);
-}
-#endif
-
 #ifndef DIP_FUSED_NSEG
 #error "compile with -DDIP_FUSED_NSEG=1 or 2 and -DDIP_FUSED_DTYPE=0, 1 or 2"
 #endif
@@ -531,22 +245,5 @@ hipError_t DIP_FUSED_NAME(DIP_FUSED_NSEG, DIP_FUSED_DTYPE)(const FusedParams& fp
 #endif
 }
 
-
-#if DIP_FUSED_NSEG == 1 && DIP_FUSED_DTYPE == 0
-hipError_t launch_select_rows(const SelectParams& p, hipStream_t stream, int pk) {
-    if (!p.v || !p.mask_out || p.rows < 1 || p.n < 1 || p.n > DIP_MAX_N || p.k < 1 || p.k > p.n)
-        return hipErrorInvalidValue;
-    const int items = (p.n + kSelThreads - 1) / kSelThreads;
-    if (items <= 2) return launch_rows_items<2>(p, stream, pk);
-    if (items <= 4) return launch_rows_items<4>(p, stream, pk);
-    if (items <= 6) return launch_rows_items<6>(p, stream, pk);
-    if (items <= 8) return launch_rows_items<8>(p, stream, pk);
-    if (items <= 11) return launch_rows_items<11>(p, stream, pk);
-    if (items <= 14) return launch_rows_items<14>(p, stream, pk);
-    if (items <= 18) return launch_rows_items<18>(p, stream, pk);
-    if (items <= 24) return launch_rows_items<24>(p, stream, pk);
-    return launch_rows_items<32>(p, stream, pk);
-}
-#endif
 
 }  // namespace dip

@@ -60,19 +60,35 @@ struct SelectParams {
     // words of the columns this update evicted / inserted (nullable; only with a cache update)
     uint32_t* evicted_out;
     uint32_t* inserted_out;
-    // rows > 1: one workgroup per row; row b reads v + b*v_row_stride and writes its mask at
-    // mask_out + b*words_row_stride (the other outputs and the cache update must be off)
-    int rows;
-    int64_t v_row_stride;
-    int64_t words_row_stride;
-    // nullable: row b (one workgroup per row; row 0 otherwise) writes the bit pattern of max |v| here
-    uint32_t* rowmax_out;
 };
 
 hipError_t launch_select(const SelectParams& p, hipStream_t stream, int prof_kind);
-// The row selections of a small batch (rows >= 1, one workgroup per row): mask_out and, if
-// given, rowmax_out only; every other output of SelectParams must be off.
-hipError_t launch_select_rows(const SelectParams& p, hipStream_t stream, int prof_kind);
+
+// ---- selections of several vectors: `rows` per layer, several layers of a stack ----------------
+// layers per launch of the stack kernels: their tables travel in the kernel arguments
+constexpr int kStackLayers = 64;
+struct RowsSelectParams {
+    const float* v;               // vector of (layer, row): v + layer * v_layer_stride + row * v_row_stride
+    int64_t v_layer_stride;
+    int64_t v_row_stride;
+    int n;
+    int rows;
+    float gamma;
+    uint32_t* mask_out;           // nullable; words, strides in words
+    int64_t mask_layer_stride;
+    int64_t mask_row_stride;
+    uint32_t* rowmax_out;         // nullable: bit pattern of max |v| per row
+    int64_t rowmax_layer_stride;
+    int32_t* idx_out;             // nullable, rows == 1 only: k ascending indices of each layer ...
+    float* val_out;               // ... and v at them
+    int64_t list_layer_stride;
+    struct Layer {
+        const uint32_t* score_bits;   // residency for Eq. 10 scores, or null for |v|
+        int k;
+        int pad;
+    } layer[kStackLayers];
+};
+hipError_t launch_select_rows(const RowsSelectParams& p, int layers, hipStream_t stream, int prof_kind);
 
 // Cache updates of several caches in one launch, one workgroup each (nothing in the token
 // that produced the masks waits for them).
@@ -186,6 +202,28 @@ hipError_t launch_fused_2_1(const FusedParams&, const GemvShape&, hipStream_t, i
 hipError_t launch_fused_2_2(const FusedParams&, const GemvShape&, hipStream_t, int);
 extern int g_fusion;              // 0: always launch selection and product apart
 
+// ---- gathered products of a stack of layers (equal shapes and formats) in one launch -------------
+struct StackProductParams {
+    int64_t row_stride;       // bytes
+    int scale_stride;
+    int n_in;
+    int n_out;                // elements per stored row (both halves of a bundled row)
+    const int32_t* idx;       // lists of layer l: idx + l * list_layer_stride, ascending
+    const float* val;
+    int64_t list_layer_stride;
+    float* out;               // sums of share g of layer l: out + l * out_layer_stride + g * n_out
+    int64_t out_layer_stride;
+    struct Layer {
+        const void* w;
+        const uint16_t* scales;
+        int k;
+        int pad;
+    } layer[kStackLayers];
+};
+int stack_shares(int dtype, int n_out, int k_max, int layers);
+hipError_t launch_stack_product(const StackProductParams& p, int dtype, int shares, int layers, hipStream_t stream,
+                                int prof_kind);
+
 // ---- small batches: union of row masks, batched gathered product, reduction ------------------
 struct UnionParams {
     const uint32_t* masks;     // [batch][words_stride]
@@ -223,13 +261,15 @@ struct BatchedReduceParams {
     int glu;                   // 1: out = up * SiLU(gate) over the two halves of a row
     float* out;
     int64_t out_stride;
+    int64_t partial_layer_stride;   // floats; several layers: one grid plane each
+    int64_t out_layer_stride;
 };
 bool batched_on_matrix_cores(int dtype, int batch, int64_t n_in, int64_t row_stride);
 int batched_strip_cols(int dtype, int batch, bool mc);
 int batched_shares(int dtype, int batch, int n_out, int k_max, bool mc);
 hipError_t launch_union(const UnionParams& p, hipStream_t stream);
 hipError_t launch_batched_gemv(const BatchedGemvParams& p, int shares, bool mc, hipStream_t stream, int prof_kind);
-hipError_t launch_batched_reduce(const BatchedReduceParams& p, hipStream_t stream);
+hipError_t launch_batched_reduce(const BatchedReduceParams& p, int layers, hipStream_t stream);
 
 // ---- two-tier residency: slot map of the HBM cache, fill list, encoded row list -----------------
 struct TierParams {

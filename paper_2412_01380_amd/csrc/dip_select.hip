@@ -26,8 +26,8 @@
 // adds with the tie-storm handling hoisted out of the per-key path, branch-free clamped
 // loads, one compare per key on the usual path where no tie is split at the threshold.
 // The forward calls run the same selection at the head of the gathered products instead
-// (dip_fused.hip); this kernel serves the stand-alone entry points, the batched rows, the
-// two-tier path and, through update_batch_kernel, every cache update.
+// (dip_fused.hip) or for many vectors at once (dip_rows.hip); this kernel serves the stand-alone
+// entry points, the two-tier path and, through update_batch_kernel, every cache update.
 #include "dip_select_device.h"
 
 namespace dip {
@@ -151,7 +151,6 @@ __device__ __forceinline__ void select_body(SelectParams& p, SelShared& sh) {
             __syncthreads();
             static_assert(kWaves == 16, "one wavefront maximum per lane of a 16-lane row");
             M = row_max_nonneg(sh.wave_max[lane & (kWaves - 1)]);
-            if (p.rowmax_out && tid == 0) p.rowmax_out[0] = __float_as_uint(M);
         }
         if (p.score_bits) {
 #pragma unroll
@@ -404,10 +403,6 @@ __device__ __forceinline__ void select_body(SelectParams& p, SelShared& sh) {
 template <int ITEMS>
 __global__ __launch_bounds__(kSelThreads) void select_kernel(SelectParams p) {
     __shared__ SelShared sh;
-    // one workgroup per row of a small batch (row 0 when there is no batch)
-    if (p.v) p.v += (size_t)blockIdx.x * p.v_row_stride;
-    if (p.mask_out) p.mask_out += (size_t)blockIdx.x * p.words_row_stride;
-    if (p.rowmax_out) p.rowmax_out += blockIdx.x;
     select_body<ITEMS>(p, sh);
 }
 
@@ -429,7 +424,6 @@ __global__ __launch_bounds__(kSelThreads) void update_batch_kernel(UpdateWork wo
     p.idx_out = nullptr; p.val_out = nullptr;
     p.c_bits = u.bits; p.c_stamp = u.stamp; p.c_meta = u.meta; p.capacity = u.capacity; p.policy = u.policy;
     p.zero_ptr = nullptr; p.zero_n = 0; p.evicted_out = nullptr; p.inserted_out = nullptr;
-    p.rows = 1; p.v_row_stride = 0; p.words_row_stride = 0; p.rowmax_out = nullptr;
     select_body<ITEMS>(p, sh);
 }
 
@@ -465,7 +459,7 @@ __global__ void zero_u32_kernel(uint32_t* p, int n) {
 
 template <int ITEMS>
 hipError_t launch_items(const SelectParams& p, hipStream_t stream, int prof_kind) {
-    return launch_timed(select_kernel<ITEMS>, dim3(p.rows > 1 ? p.rows : 1), dim3(kSelThreads), stream, prof_kind, p);
+    return launch_timed(select_kernel<ITEMS>, dim3(1), dim3(kSelThreads), stream, prof_kind, p);
 }
 
 template <int ITEMS>

@@ -198,3 +198,18 @@ def test_stack_and_no_alloc_argument_validation(D):
     assert L.dip_swiglu_mlp_forward_noalloc(C.byref(big), FAKE, 8192, 16384, None, None, 0.2, FAKE, None,
                                             None) == D.DIP_ERR_WORKSPACE
     assert "built-in" in D.dip_last_error()
+
+
+@pytest.mark.parametrize("dtype,d,f", [(0, 512, 1536), (1, 5120, 17920), (1, 520, 1544), (2, 640, 1408)])
+def test_stack_workspace_serves_every_part_of_the_stack(D, dtype, d, f):
+    """A caller may run any range of a stack's layers in the workspace sized for all of them."""
+    from paper_2412_01380_amd.libdip import _Mlp
+    L = D.lib
+    n = 70
+    mlps = (_Mlp * n)(*[_Mlp(_weight(D, dtype, d, 2 * f), _weight(D, dtype, f, d)) for _ in range(n)])
+    for m in mlps:
+        m.w_ug.scales = m.w_d.scales = FAKE if dtype == D.DIP_INT4_G128 else None
+    for k1, k2 in ((1, 1), (d // 3, f // 3), (d, f)):
+        ks = [(C.c_int32 * n)(*([k] * n)) for k in (k1, k2)]
+        sizes = [L.dip_swiglu_mlp_forward_stack_workspace_bytes(mlps, m, ks[0], ks[1]) for m in range(1, n + 1)]
+        assert all(a > 0 and a <= b for a, b in zip(sizes, sizes[1:]))

@@ -1,0 +1,139 @@
+"""Stack calls that run phase by phase (four or more consecutive layers of one shape): selections,
+products and reductions of all layers in one launch each, against per-layer calls and the
+oracle, at the edges of the product kernel's tiles (64-lane strips of 256 / 512 / 1024 columns,
+blocks of 8 selected rows, 8 wavefronts, shares)."""
+import numpy as np
+import pytest
+import torch
+
+from oracle import dip_oracle as O
+from workloads import ar1_laplace_stream, layer_weights
+from gpu_util import assert_product_close, dev_f32, host_u32, make_weight, workspace
+
+pytestmark = pytest.mark.gpu
+
+
+@pytest.fixture(scope="module")
+def D():
+    import paper_2412_01380_amd as D
+    return D
+
+
+def _layers(D, dims, fmt):
+    ws = [layer_weights(d, f, seed=71, layer=l, dtype=fmt) for l, (d, f) in enumerate(dims)]
+    return ws, [D.Mlp(make_weight(D, w["ug"]), make_weight(D, w["d"])) for w in ws]
+
+
+def _caches(D, dims, policy=0):
+    cs = [[D.Cache(d, d // 2, policy) for d, _ in dims], [D.Cache(f, f // 2, policy) for _, f in dims]]
+    for c in cs[0] + cs[1]:
+        D.dip_cache_init(c)
+    return cs
+
+
+def _check(D, dims, fmt, k_in, k_mid, use_cache, tokens=3):
+    """A stack call per token against per-layer calls on a second set of caches: y against the
+    oracle's product of the per-layer call's h and mask, cache states bit for bit."""
+    ws, mlps = _layers(D, dims, fmt)
+    L, d = len(dims), dims[0][0]
+    a, b = (_caches(D, dims), _caches(D, dims)) if use_cache else ((None, None), (None, None))
+    stack = D.MlpStack(mlps, a[0], a[1])
+    buf = workspace(D.dip_swiglu_mlp_forward_stack_workspace_bytes(stack, k_in, k_mid))
+    buf.fill_(0xFF)       # nothing is expected of the workspace's contents
+    one = workspace(max(D.dip_swiglu_mlp_forward_workspace_bytes(m, k_in[l], k_mid[l]) for l, m in enumerate(mlps)))
+    X = dev_f32(ar1_laplace_stream(L * tokens, d, seed=72).reshape(tokens, L, d))
+    Y = torch.full((L, d), float("nan"), device="cuda")
+    y1 = torch.empty(d, device="cuda")
+    for t in range(tokens):
+        D.dip_swiglu_mlp_forward_stack(stack, X[t], d, k_in, k_mid, 0.2, Y, d, buf)
+        for l, (_, f) in enumerate(dims):
+            dbg = D.Debug(d, f, k_in[l], k_mid[l])
+            D.dip_swiglu_mlp_forward(mlps[l], X[t, l], k_in[l], k_mid[l], b[0] and b[0][l], b[1] and b[1][l], 0.2, y1, dbg, one)
+            torch.cuda.synchronize()
+            ref = O.gathered_gemv(ws[l]["d"], dbg.h.cpu().numpy(), dbg.idx_mid.cpu().numpy())
+            # h of the two calls differs by the rounding of its own sums (k_in terms, then SwiGLU)
+            assert_product_close(Y[l].cpu().numpy(), ref, fmt, max(k_in[l], k_mid[l]), (t, l, "y"), factor=4.0)
+            if use_cache:
+                for p, q in ((a[0][l], b[0][l]), (a[1][l], b[1][l])):
+                    assert torch.equal(p.bits, q.bits) and torch.equal(p.stamp, q.stamp) and torch.equal(p.meta, q.meta), (t, l)
+
+
+@pytest.mark.parametrize("fmt,d,f", [("f32", 516, 1540), ("bf16", 520, 1544), ("bf16", 1032, 2056), ("int4", 640, 1408)])
+def test_stack_edges_of_tiles_blocks_and_shares(D, fmt, d, f):
+    # per-layer k: below, at and above one block and one round of blocks, a prime, everything
+    k_in = [1, 7, 8, 9, 63, 64, 65, d - 1, d]
+    k_mid = [d, 65, 64, 63, 9, 8, 7, 1, f]
+    _check(D, [(d, f)] * 9, fmt, k_in, k_mid, use_cache=True)
+
+
+def test_stack_of_runs_and_single_layers(D):
+    """Phases for the runs, layer by layer in between: both share one scratch area."""
+    dims = [(512, 1536)] * 4 + [(512, 2304)] + [(512, 1024)] * 5 + [(512, 1536)] * 2
+    L = len(dims)
+    _check(D, dims, "bf16", [150] * L, [400 + 8 * l for l in range(L)], use_cache=True)
+    _check(D, dims, "f32", [150] * L, [400 + 8 * l for l in range(L)], use_cache=False)
+
+
+def test_stack_longer_than_one_table(D):
+    _check(D, [(256, 512)] * 70, "bf16", [80] * 70, [200] * 70, use_cache=True, tokens=2)
+
+
+def test_stack_layers_chained_through_their_buffers(D):
+    """y of layer l is x of layer l + 1: such a call runs its layers one after the other."""
+    dims, k_in, k_mid = [(512, 1536)] * 5, 160, 500
+    _, mlps = _layers(D, dims, "bf16")
+    stack = D.MlpStack(mlps)
+    buf = workspace(D.dip_swiglu_mlp_forward_stack_workspace_bytes(stack, k_in, k_mid))
+    chain = torch.zeros(6, 512, device="cuda")
+    chain[0] = dev_f32(ar1_laplace_stream(1, 512, seed=3)[0])
+    want = chain.clone()
+    D.dip_swiglu_mlp_forward_stack(stack, chain, 512, k_in, k_mid, 0.2, chain[1:], 512, buf)
+    for l in range(5):
+        D.dip_swiglu_mlp_forward(mlps[l], want[l], k_in, k_mid, None, None, 0.2, want[l + 1], None, buf)
+    torch.cuda.synchronize()
+    assert torch.equal(chain.view(torch.int32), want.view(torch.int32))
+    # in place (y over its own x) keeps the phases
+    x = dev_f32(ar1_laplace_stream(5, 512, seed=4))
+    y = torch.empty_like(x)
+    D.dip_swiglu_mlp_forward_stack(stack, x, 512, k_in, k_mid, 0.2, y, 512, buf)
+    D.dip_swiglu_mlp_forward_stack(stack, x, 512, k_in, k_mid, 0.2, x, 512, buf)
+    torch.cuda.synchronize()
+    assert torch.equal(x.view(torch.int32), y.view(torch.int32))
+
+
+def test_stack_of_non_finite_inputs_ends(D):
+    dims = [(512, 1536)] * 4
+    _, mlps = _layers(D, dims, "bf16")
+    stack = D.MlpStack(mlps)
+    buf = workspace(D.dip_swiglu_mlp_forward_stack_workspace_bytes(stack, 160, 500))
+    buf.fill_(0xFF)
+    x = torch.randn(4, 512, device="cuda")
+    x[0, 3], x[1, ::2], x[2] = float("inf"), float("nan"), float("nan")
+    y = torch.empty_like(x)
+    D.dip_swiglu_mlp_forward_stack(stack, x, 512, 160, 500, 0.2, y, 512, buf)
+    torch.cuda.synchronize()
+    assert torch.isfinite(y[3]).all()
+
+
+@pytest.mark.parametrize("fmt", ["bf16", "int4"])
+def test_stack_phases_replay_from_a_graph(D, fmt):
+    dims, k_in, k_mid, L = [(512, 1536)] * 6, 150, 500, 6
+    _, mlps = _layers(D, dims, fmt)
+    ce, cg = _caches(D, dims), _caches(D, dims)
+    se, sg = D.MlpStack(mlps, *ce), D.MlpStack(mlps, *cg)
+    n = D.dip_swiglu_mlp_forward_stack_workspace_bytes(se, k_in, k_mid)
+    we, wg = workspace(n), workspace(n)
+    X = dev_f32(ar1_laplace_stream(L * 5, 512, seed=8).reshape(5, L, 512))
+    xb, ye, yg = torch.zeros(L, 512, device="cuda"), torch.empty(L, 512, device="cuda"), torch.zeros(L, 512, device="cuda")
+    torch.cuda.synchronize()
+    graph = torch.cuda.CUDAGraph()
+    with torch.cuda.graph(graph):
+        D.dip_swiglu_mlp_forward_stack(sg, xb, 512, k_in, k_mid, 0.2, yg, 512, wg)
+    for t in range(5):
+        D.dip_swiglu_mlp_forward_stack(se, X[t], 512, k_in, k_mid, 0.2, ye, 512, we)
+        xb.copy_(X[t])
+        graph.replay()
+        torch.cuda.synchronize()
+        assert torch.equal(ye.view(torch.int32), yg.view(torch.int32)), t
+        for a, b in zip(ce[0] + ce[1], cg[0] + cg[1]):
+            assert np.array_equal(host_u32(a.bits), host_u32(b.bits)) and a.meta_host() == b.meta_host(), t
