@@ -38,6 +38,13 @@ constexpr int kUnionWordsPerWg = kUnionThreads / 32;   // one lane per feature o
 // row and the feature's activations -- is requested before anything is waited for: the kernel
 // is one memory round trip, a scan and the stores.
 __global__ __launch_bounds__(kUnionThreads) void union_kernel(UnionParams p) {
+    const int layer = blockIdx.y;
+    p.masks += layer * p.masks_layer_stride;
+    p.x += layer * p.x_layer_stride;
+    p.union_words += layer * p.union_layer_stride;
+    p.uidx += layer * p.list_layer_stride;
+    p.uval += layer * p.list_layer_stride * p.batch;
+    p.count_out += layer;
     __shared__ uint32_t s_base[2 * kUnionThreads];
     __shared__ uint32_t s_wave[kUnionThreads / 64];
     constexpr int kMaxBatch = 8;
@@ -254,7 +261,13 @@ __global__ __launch_bounds__(kBWaves * 64) void bgemv_kernel(BatchedGemvParams p
     // lanes past the right edge of a ragged last strip re-read its last piece; they own no output
     const int col = col_raw < p.n_out ? col_raw : p.n_out - EPL;
 
-    const int k = min((int)p.k_dev[0], p.k_max);
+    const int layer = blockIdx.z;
+    // (the parameters stay untouched: a table in them indexed by the layer is read from where it
+    //  is only as long as nothing writes to them)
+    const int32_t* uidx = p.uidx + layer * p.list_layer_stride;
+    const float* uval = p.uval + layer * p.list_layer_stride * B;
+    const uint16_t* scales = p.layer[layer].scales;
+    const int k = min((int)p.k_dev[layer], p.k_max);
     const int share = ((k + G - 1) / G + U - 1) / U * U;
     const int kb = min(k, g * share), ke = min(k, kb + share);
 
@@ -267,12 +280,12 @@ __global__ __launch_bounds__(kBWaves * 64) void bgemv_kernel(BatchedGemvParams p
         for (int e = 0; e < EPL; ++e) acc[b][e] = 0.f;
     }
 
-    const char* wbase = static_cast<const char*>(p.w) + (size_t)col * E::kBits / 8;
+    const char* wbase = static_cast<const char*>(p.layer[layer].w) + (size_t)col * E::kBits / 8;
     const int sgroup = col >> 7;
     // a lane group takes U consecutive listed columns per step; the lists are padded so that
     // whole vectors can be read past position k, and what lies past the share is dropped
     for (int t0 = kb + (wave * RPW + sub) * U; t0 < ke; t0 += NG * U) {
-        const int4 r4 = *reinterpret_cast<const int4*>(p.uidx + t0);
+        const int4 r4 = *reinterpret_cast<const int4*>(uidx + t0);
         const int r[U] = {r4.x, r4.y, r4.z, r4.w};
         typename E::raw_t q[U];
         float scale[U];
@@ -286,11 +299,11 @@ __global__ __launch_bounds__(kBWaves * 64) void bgemv_kernel(BatchedGemvParams p
             scale[u] = 1.f;
             if constexpr (E::kScaled) {
                 _Float16 hs;
-                const uint16_t raw = p.scales[(size_t)rr * p.scale_stride + sgroup];
+                const uint16_t raw = scales[(size_t)rr * p.scale_stride + sgroup];
                 __builtin_memcpy(&hs, &raw, 2);
                 scale[u] = (float)hs;
             }
-            load_mult<B>(p.uval + (size_t)(t0 + u) * B, m[u]);
+            load_mult<B>(uval + (size_t)(t0 + u) * B, m[u]);
         }
 #pragma unroll
         for (int u = 0; u < U; ++u) {
@@ -336,7 +349,7 @@ __global__ __launch_bounds__(kBWaves * 64) void bgemv_kernel(BatchedGemvParams p
         const int b = o / SC, c = o % SC;
         const int gcol = strip * SC + c;
         if (gcol >= p.n_out) continue;
-        p.partial[((size_t)g * B + b) * (size_t)p.n_out + gcol] = red[b][c];
+        p.partial[layer * p.partial_layer_stride + ((size_t)g * B + b) * (size_t)p.n_out + gcol] = red[b][c];
     }
 }
 
@@ -406,7 +419,12 @@ __global__ __launch_bounds__(kMWaves * 64) void bgemv_q4_mfma_kernel(BatchedGemv
     const int B = p.batch;
     const int ngroups = p.n_out >> 7;
 
-    const int k = min((int)p.k_dev[0], p.k_max);
+    const int layer = blockIdx.z;
+    const int32_t* uidx = p.uidx + layer * p.list_layer_stride;
+    const float* uval = p.uval + layer * p.list_layer_stride * B;
+    const uint32_t* rowmax = p.rowmax + 8 * layer;
+    const uint16_t* scales = p.layer[layer].scales;
+    const int k = min((int)p.k_dev[layer], p.k_max);
     const int share = ((k + G - 1) / G + kMRowSet - 1) / kMRowSet * kMRowSet;
     const int kb = min(k, g * share), ke = min(k, kb + share);
 
@@ -431,13 +449,13 @@ __global__ __launch_bounds__(kMWaves * 64) void bgemv_q4_mfma_kernel(BatchedGemv
     constexpr int STEP = kMWaves * kMRowSet;
     // (the lists carry 16 spare entries past k_max, so whole index vectors may be read there)
     auto load_idx = [&](int t) {
-        return *reinterpret_cast<const int4*>(p.uidx + min(t, p.k_max) + 4 * r);
+        return *reinterpret_cast<const int4*>(uidx + min(t, p.k_max) + 4 * r);
     };
-    const char* wbytes = static_cast<const char*>(p.w);
+    const char* wbytes = static_cast<const char*>(p.layer[layer].w);
     const uint32_t row_stride = (uint32_t)p.row_stride;
     const uint32_t wcol[kMGroups] = {(uint32_t)(grp[0] * 64 + 4 * c), (uint32_t)(grp[1] * 64 + 4 * c)};
     const uint32_t cb = (uint32_t)min(c, B - 1);
-    const float row_up = row_scale_up(p.rowmax[cb]);     // this lane's batch row, into [8, 16)
+    const float row_up = row_scale_up(rowmax[cb]);     // this lane's batch row, into [8, 16)
     int4 rn = load_idx(kb + wave * kMRowSet);
     for (int t0 = kb + wave * kMRowSet; t0 < ke; t0 += STEP) {
         const int rows[4] = {rn.x, rn.y, rn.z, rn.w};
@@ -454,14 +472,14 @@ __global__ __launch_bounds__(kMWaves * 64) void bgemv_q4_mfma_kernel(BatchedGemv
             // entries past the share hold whatever the list memory held: they are masked out
             // of the left operand bit-wise (never multiplied away), and the mask is plain
             // arithmetic so that the load stays unconditional
-            mv[i] = p.uval[(uint32_t)min(u, p.k_max - 1) * (uint32_t)B + cb] * row_up;
+            mv[i] = uval[(uint32_t)min(u, p.k_max - 1) * (uint32_t)B + cb] * row_up;
             if (live && row_live) keep[i >> 1] |= (i & 1) ? 0xffff0000u : 0x0000ffffu;
             const uint32_t wrow = rr * row_stride;
             const uint32_t srow = rr * (uint32_t)p.scale_stride;
 #pragma unroll
             for (int gg = 0; gg < kMGroups; ++gg) {
                 wq[gg][i] = *reinterpret_cast<const uint32_t*>(wbytes + (wrow + wcol[gg]));
-                sc[gg][i] = p.scales[srow + (uint32_t)grp[gg]];
+                sc[gg][i] = scales[srow + (uint32_t)grp[gg]];
             }
         }
 #pragma unroll
@@ -539,8 +557,8 @@ __global__ __launch_bounds__(kMWaves * 64) void bgemv_q4_mfma_kernel(BatchedGemv
         const int gcol = strip * kMStripCols + cc;
         if (gcol >= p.n_out) continue;
         const int gg = cc >> 7, cl = (cc & 127) >> 3, t = cc & 7;
-        const float row_down = 1.0f / row_scale_up(p.rowmax[b]);     // a power of two: exact
-        p.partial[((size_t)g * B + b) * (size_t)p.n_out + gcol] = fmaf(-8.0f, red1[gg][b], red[gg][t][b][cl]) * row_down;
+        const float row_down = 1.0f / row_scale_up(rowmax[b]);     // a power of two: exact
+        p.partial[layer * p.partial_layer_stride + ((size_t)g * B + b) * (size_t)p.n_out + gcol] = fmaf(-8.0f, red1[gg][b], red[gg][t][b][cl]) * row_down;
     }
 }
 
@@ -604,28 +622,34 @@ int batched_strip_cols(int dtype, int batch, bool mc) {
     return dtype == DIP_F32 ? 16 * 4 : (dtype == DIP_BF16 ? 16 * 8 : 32 * 16);
 }
 
-int batched_shares(int dtype, int batch, int n_out, int k_max, bool mc) {
+int batched_shares(int dtype, int batch, int n_out, int k_max, bool mc, int layers) {
     // Vector-ALU product: about 1024 workgroups, at least 32 listed columns each.
     // Matrix-core product: one round of workgroups -- three of them fit a compute unit, 768
     // in all; 840 take as long as 1536 -- and at least one set of 16 per wavefront.
+    // Over several layers there are workgroups enough: shares of at most kLong listed columns
+    // keep the last round short, and every share costs a write and a read of its sums.
     const int sc = batched_strip_cols(dtype, batch, mc);
-    const int strips = (n_out + sc - 1) / sc;
+    const int strips = (n_out + sc - 1) / sc * layers;
     const int min_rows = mc ? kMWaves * kMRowSet : 32;
+    const int kLong = mc ? 2048 : 512;
     int g = mc ? 768 / strips : (1024 + strips - 1) / strips;
+    if (layers > 1 && g < (k_max + kLong - 1) / kLong) g = (k_max + kLong - 1) / kLong;
     while (g > 1 && k_max / g < min_rows) --g;
     return g < 1 ? 1 : g;
 }
 
-hipError_t launch_union(const UnionParams& p, hipStream_t stream) {
+hipError_t launch_union(const UnionParams& p, int layers, hipStream_t stream) {
     const int nwords = (p.n + 31) >> 5;
-    hipLaunchKernelGGL(union_kernel, dim3((nwords + kUnionWordsPerWg - 1) / kUnionWordsPerWg),
+    hipLaunchKernelGGL(union_kernel, dim3((nwords + kUnionWordsPerWg - 1) / kUnionWordsPerWg, layers),
                        dim3(kUnionThreads), 0, stream, p);
     return hipGetLastError();
 }
 
-hipError_t launch_batched_gemv(const BatchedGemvParams& p, int shares, bool mc, hipStream_t stream, int pk) {
+hipError_t launch_batched_gemv(const BatchedGemvParams& p, int shares, bool mc, int layers, hipStream_t stream,
+                               int pk) {
     const int sc = batched_strip_cols(p.dtype, p.batch, mc);
-    dim3 grid((p.n_out + sc - 1) / sc, shares);
+    dim3 grid((p.n_out + sc - 1) / sc, shares, layers);
+    if (layers < 1 || layers > kStackLayers) return hipErrorInvalidValue;
     if (mc) {
         if (!p.rowmax || p.dtype != DIP_INT4_G128 || (int64_t)p.n_in * p.row_stride >= ((int64_t)1 << 32))
             return hipErrorInvalidValue;

@@ -225,33 +225,43 @@ hipError_t launch_stack_product(const StackProductParams& p, int dtype, int shar
                                 int prof_kind);
 
 // ---- small batches: union of row masks, batched gathered product, reduction ------------------
+// (several layers of one shape and format: one grid plane each, `*_layer_stride` apart)
 struct UnionParams {
     const uint32_t* masks;     // [batch][words_stride]
     int64_t words_stride;
+    int64_t masks_layer_stride;
     const float* x;            // [batch][x_stride] activations the masks were taken from
     int64_t x_stride;
+    int64_t x_layer_stride;
     int n;
     int batch;
     uint32_t* union_words;     // ceil(n/32)
+    int64_t union_layer_stride;
     int32_t* uidx;             // ascending indices of the union, up to min(n, batch*k)
     float* uval;               // [listed][batch]: x[b][i] if row b selected i, else 0
-    uint32_t* count_out;       // number of listed indices
+    int64_t list_layer_stride; // entries (uval: times batch)
+    uint32_t* count_out;       // number of listed indices, one word per layer
 };
 struct BatchedGemvParams {
-    const void* w;
     int64_t row_stride;
-    const uint16_t* scales;
     int scale_stride;
     int dtype;
     int n_in;
     int n_out;                 // full stored row width
     const int32_t* uidx;
     const float* uval;
-    const uint32_t* k_dev;     // listed columns (device)
+    int64_t list_layer_stride;
+    const uint32_t* k_dev;     // listed columns (device), one word per layer
     int k_max;                 // capacity of the lists
     int batch;
     float* partial;            // [shares][batch][n_out]
-    const uint32_t* rowmax;    // [batch] bit patterns of max |x[b]| from the row selection (matrix-core product only)
+    int64_t partial_layer_stride;
+    const uint32_t* rowmax;    // [batch] bit patterns of max |x[b]| from the row selection (matrix-core product
+                               // only), 8 words per layer
+    struct Layer {
+        const void* w;
+        const uint16_t* scales;
+    } layer[kStackLayers];
 };
 struct BatchedReduceParams {
     const float* partial;
@@ -266,9 +276,10 @@ struct BatchedReduceParams {
 };
 bool batched_on_matrix_cores(int dtype, int batch, int64_t n_in, int64_t row_stride);
 int batched_strip_cols(int dtype, int batch, bool mc);
-int batched_shares(int dtype, int batch, int n_out, int k_max, bool mc);
-hipError_t launch_union(const UnionParams& p, hipStream_t stream);
-hipError_t launch_batched_gemv(const BatchedGemvParams& p, int shares, bool mc, hipStream_t stream, int prof_kind);
+int batched_shares(int dtype, int batch, int n_out, int k_max, bool mc, int layers);
+hipError_t launch_union(const UnionParams& p, int layers, hipStream_t stream);
+hipError_t launch_batched_gemv(const BatchedGemvParams& p, int shares, bool mc, int layers, hipStream_t stream,
+                               int prof_kind);
 hipError_t launch_batched_reduce(const BatchedReduceParams& p, int layers, hipStream_t stream);
 
 // ---- two-tier residency: slot map of the HBM cache, fill list, encoded row list -----------------

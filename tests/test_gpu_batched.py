@@ -188,3 +188,38 @@ def test_batched_stack_call_equals_per_layer_calls(D, fmt, B):
             assert torch.equal(Y[l].view(torch.int32), Y1.view(torch.int32)), (t, l, "y")
             for a, b in ((caches[0][l], caches[2][l]), (caches[1][l], caches[3][l])):
                 assert torch.equal(a.bits, b.bits) and torch.equal(a.stamp, b.stamp) and torch.equal(a.meta, b.meta), (t, l)
+
+
+@pytest.mark.parametrize("fmt,B", [("f32", 5), ("bf16", 3), ("int4", 2), ("int4", 7)])
+def test_batched_stack_in_phases_matches_per_layer_calls(D, fmt, B):
+    """Layers of one shape run phase by phase (one launch per phase for all of them), with k per
+    layer at the edges of the product kernels' steps: y of every layer within the rounding of
+    another split of the sums, cache states bit for bit."""
+    d, f, L = 640, 1408, 6
+    k_in, k_mid = [1, 15, 16, 17, 200, d], [33, 32, 31, f, 1, 500]
+    mlps = []
+    for l in range(L):
+        w = layer_weights(d, f, seed=63, layer=l, dtype=fmt)
+        mlps.append(D.Mlp(make_weight(D, w["ug"]), make_weight(D, w["d"])))
+    caches = [[D.Cache(d, 200) for _ in range(L)], [D.Cache(f, f // 2) for _ in range(L)],
+              [D.Cache(d, 200) for _ in range(L)], [D.Cache(f, f // 2) for _ in range(L)]]
+    for c in sum(caches, []):
+        D.dip_cache_init(c)
+    stack = D.MlpStack(mlps, caches[0], caches[1])
+    ws = workspace(D.dip_swiglu_mlp_forward_batched_stack_workspace_bytes(stack, B, k_in, k_mid))
+    ws.fill_(0xFF)        # nothing is expected of the workspace's contents
+    one = workspace(max(D.dip_swiglu_mlp_forward_batched_workspace_bytes(mlps[l], B, k_in[l], k_mid[l]) for l in range(L)))
+    Y = torch.full((L, B, d), float("nan"), device="cuda")
+    Y1 = torch.empty(B, d, dtype=torch.float32, device="cuda")
+    tol = 2e-4 if fmt == "int4" and B >= 3 else 2e-6      # the matrix-core product's own bar; fp32 sums in another order
+    for t in range(3):
+        X = dev_f32(np.stack([ar1_laplace_stream(t + 1, d, seed=700 + l * 8 + b)[t] for l in range(L) for b in range(B)])
+                    .reshape(L, B, d))
+        D.dip_swiglu_mlp_forward_batched_stack(stack, X, B * d, B, k_in, k_mid, 0.2, Y, B * d, ws)
+        for l in range(L):
+            D.dip_swiglu_mlp_forward_batched(mlps[l], X[l], B, k_in[l], k_mid[l], caches[2][l], caches[3][l], 0.2, Y1,
+                                             None, None, None, one)
+            torch.cuda.synchronize()
+            assert rel_l2(Y[l].cpu().numpy(), Y1.cpu().numpy()) <= tol, (t, l)
+            for a, b in ((caches[0][l], caches[2][l]), (caches[1][l], caches[3][l])):
+                assert torch.equal(a.bits, b.bits) and torch.equal(a.stamp, b.stamp) and torch.equal(a.meta, b.meta), (t, l)
