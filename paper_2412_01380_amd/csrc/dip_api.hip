@@ -752,8 +752,8 @@ BatchedPlan plan_batched(const dip_mlp* mlp, int B, const int32_t* k_in, const i
     // (a workspace sized for a stack serves every part of it: fewer layers get more shares each)
     size_t part_words = 0;
     for (int m = 1; m <= layers; ++m) {
-        pl.g1 = batched_shares(mlp->w_ug.dtype, B, 2 * pl.f, pl.k1max, pl.mc1, m);
-        pl.g2 = batched_shares(mlp->w_d.dtype, B, pl.d, pl.k2max, pl.mc2, m);
+        pl.g1 = batched_shares(mlp->w_ug.dtype, 2 * pl.f, pl.k1max, pl.mc1, m);
+        pl.g2 = batched_shares(mlp->w_d.dtype, pl.d, pl.k2max, pl.mc2, m);
         pl.part = align_up(std::max((size_t)pl.g1 * B * 2 * pl.f, (size_t)pl.g2 * B * pl.d), 64);
         part_words = std::max(part_words, pl.part * m);
     }
@@ -858,7 +858,7 @@ int32_t batched_group(const dip_mlp* mlps, int layers, const float* X, int64_t x
         up.masks = q.masks; up.words_stride = q.words; up.masks_layer_stride = q.masks_stride;
         up.x = q.v; up.x_stride = q.n; up.x_layer_stride = q.v_stride; up.n = q.n; up.batch = batch;
         up.union_words = uwords + pt * kMaskWords; up.union_layer_stride = 2 * kMaskWords;
-        up.uidx = q.uidx; up.uval = q.uval; up.list_layer_stride = q.list; up.count_out = cnt + layers * pt;
+        up.uidx = q.uidx; up.uval = q.uval; up.list_layer_stride = q.list; up.count_out = cnt + layers * pt; up.row_major = q.mc ? 1 : 0;
         if ((st = check_hip(launch_union(up, layers, hs), "forward_batched: union"))) return st;
         // one cache update with the union mask (Alg. 1 step 3), run by the caller
         for (int l = 0; q.caches && l < layers; ++l)

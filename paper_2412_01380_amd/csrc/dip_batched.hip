@@ -112,7 +112,11 @@ __global__ __launch_bounds__(kUnionThreads) void union_kernel(UnionParams p) {
 #pragma unroll
     for (int b = 0; b < kMaxBatch; ++b) m[b] = ((rows >> b) & 1u) ? xv[b] : 0.f;
     float* dst = p.uval + (size_t)pos * B;
-    if (B == 8) {
+    if (p.row_major) {
+#pragma unroll
+        for (int b = 0; b < kMaxBatch; ++b)
+            if (b < B) p.uval[b * p.list_layer_stride + pos] = m[b];
+    } else if (B == 8) {
         reinterpret_cast<float4*>(dst)[0] = make_float4(m[0], m[1], m[2], m[3]);
         reinterpret_cast<float4*>(dst)[1] = make_float4(m[4], m[5], m[6], m[7]);
     } else if (B == 4) {
@@ -354,49 +358,64 @@ __global__ __launch_bounds__(kBWaves * 64) void bgemv_kernel(BatchedGemvParams p
 }
 
 // ---------------------------------------------------------------------------------------
-// int4-g128 weights, more than kMfmaMinBatch rows: the product on the matrix cores.
+// int4-g128 weights, kMfmaMinBatch rows and more: the product on the matrix cores.
 //
 // With B rows the union columns times the row multipliers is a dense contraction
 //     P[b][j] = sum_u  m[b][u] * scale[u][j / 128] * q[u][j],
 // B x K_union x n_out, and on the vector ALU every 4-bit code costs B multiply-adds plus its
-// unpacking.  v_mfma_f32_16x16x16_f16 takes it instead: M = batch row (16, the rows past B are
-// zero), K = 16 listed columns, N = 16 stored columns.  The scale belongs to (u, 128-column
-// group), so it goes into the left operand next to the multiplier: m * scale enters as the
-// sum of two fp16 numbers (its rounded value and the rounded rest; each tile is multiplied
-// twice).  fp16 has a fixed range, and the re-weighting of Sec. 5.2 normalises by ||x||_inf
-// precisely so that the dynamic range of the activations does not matter: every batch row is
-// therefore multiplied by the power of two that brings its largest |activation| into [8, 16)
-// before the split -- exact in fp32 -- and the partial sums are multiplied by the inverse
-// power when they are stored, also exact.  The product then depends on the weights only:
-// with |m| < 16 it stays inside the fp16 range for group scales up to 4094, and the second
-// term (an fp16 denormal as a rule, absolute step 6e-8) carries m * scale to about 2^-21 of
-// the row's largest product whatever the magnitude of the activations.  The right operand
-// holds the codes q + 8 in [0, 15], exact in fp16.  Sums are fp32; the offset leaves as
-// -8 * sum_u m*scale, which a product with an all-ones right operand supplies.
+// unpacking.  v_mfma_f32_16x16x32_f16 takes it instead: K = 32 listed columns, N = 16 stored
+// columns.  The scale belongs to (u, 128-column group), so it goes into the left operand next to
+// the multiplier, and m * scale enters as the sum of two fp16 numbers: its significand cut to
+// 11 bits, and the rest times 2^10.  A batch has at most 8 rows and the operand has 16: rows
+// 0-7 hold the (negated) first terms, rows 8-15 the second ones, so one product takes both.
+// fp16 has a fixed range, and the re-weighting of Sec. 5.2 normalises by ||x||_inf precisely so
+// that the dynamic range of the activations does not matter: every batch row is therefore
+// multiplied by the power of two that brings its largest |activation| into [8, 16) before the
+// split -- exact in fp32 -- and the partial sums are multiplied by the inverse power when they
+// are stored, also exact.  The product then depends on the weights only: with |m| < 16 it stays
+// inside the fp16 range for group scales up to 4094, and the two terms carry m * scale to 2^-21
+// of its value (to 2^-25 absolute where it lies below the fp16 normal range).
 //
-// Lane l of a wavefront: k-block r = l / 16 (listed columns 4r .. 4r+3 of the 16), c = l % 16.
-// Right operand: the lane loads one dword = 8 codes of each of its 4 stored rows at byte 4c of
-// the group's 64-byte piece; product number t (0..7) takes code t of the four dwords, so it
-// yields the stored columns 8c + t.  Left operand: the lane is batch row c; it multiplies that
-// row's multiplier of its 4 listed columns by the scale of (column, group).
-// A workgroup covers two groups (256 stored columns, one 128-byte piece per row) and a share
-// of the listed columns; its wavefronts take sets of 16 listed columns in turn.
+// The right operand holds the codes themselves, exact in fp16.  Lane l of a wavefront, k-block
+// r = l / 16, c = l % 16, loads 8 bytes = 16 codes of each of its 8 stored rows (listed columns
+// 8r .. 8r+7 of the 32) at byte 8c of the 128-byte piece of two groups: whole cache lines, read
+// past the caches.  Lanes 0-7 then hold group 0 and lanes 8-15 group 1; one rotation of the row of
+// 16 lanes per dword gives lanes 8-15 the second dwords of lanes 0-7 and the other way round, after
+// which both registers hold one group each, 8 codes per lane.  A byte permute joins the halves of
+// two rows' dwords; two nibbles 16 bits apart, masked and completed in place by one three-operand
+// logic instruction, are the fp16 numbers 1024 + (q + 8) (bits 0-3) or 1024 + 16 (q + 8) (bits 4-7),
+// and a packed add leaves q or 16 q: 20 instructions for 16 codes of product t (0..7) = code t of
+// the rows, where a conversion per code took 40.  (The masked nibbles alone, as fp16 denormals,
+// save the add, but the matrix cores align the terms of a sum by the exponent field, and small
+// terms beside large ones lose as many bits as the denormals have leading zeros: errors of 3e-5
+// instead of 3e-7 where every column is listed.)  Product t yields the stored columns 16c + t
+// (c < 8) and 16(c - 8) + 8 + t of its group; the factor 16 leaves at the end; sums are fp32.
+//
+// Row indices, multipliers ([batch row][listed column]) and scales ([group][listed column]) of up
+// to kMChunk listed columns are staged in LDS, so that a step is six 16-byte LDS reads and eight
+// loads of codes, and the codes of the next kMAhead sets are in flight while one is multiplied.  A
+// wavefront covers two groups (256 stored columns, 128 bytes of a row) and the four of a workgroup
+// lie side by side (KW == 1: 512 bytes of a row, every wavefront takes all sets of 32 listed
+// columns and no sum crosses wavefronts) or, where that gives too few workgroups, take the sets of
+// one strip in turn (KW == 4).
+//
+// Bound: HBM and instruction issue side by side.  40 layers of the Phi-3-Medium shape, 8 rows, up /
+// gate product: 2.1 GB of codes in 436 us, where the loads alone take 359 us and the arithmetic
+// alone about as long (330 vector and 16 matrix instructions per 32 x 256 codes); down product
+// 333 us.  The conversion-per-code form with K = 16 and a matrix product per term took 781 and
+// 516 us; three workgroups per compute unit with one set ahead 519 and 351 us.
 // ---------------------------------------------------------------------------------------
-typedef _Float16 h4_t __attribute__((ext_vector_type(4)));
+typedef _Float16 h8_t __attribute__((ext_vector_type(8)));
 typedef float f4_t __attribute__((ext_vector_type(4)));
 
 constexpr int kMfmaMinBatch = 3;
 constexpr int kMWaves = 4;
-constexpr int kMGroups = 2;
-constexpr int kMStripCols = 128 * kMGroups;
-constexpr int kMRowSet = 16;
-
-__device__ __forceinline__ h4_t pack_h4(float a, float b, float c, float d) {
-    // round-toward-zero packing is exact here: the values are integers in [0, 15]
-    struct { decltype(__builtin_amdgcn_cvt_pkrtz(0.f, 0.f)) lo, hi; } v = {__builtin_amdgcn_cvt_pkrtz(a, b),
-                                                                         __builtin_amdgcn_cvt_pkrtz(c, d)};
-    return __builtin_bit_cast(h4_t, v);
-}
+constexpr int kMGroups = 2;                    // groups of 128 stored columns per wavefront
+constexpr int kMWaveCols = 128 * kMGroups;
+constexpr int kMRowSet = 32;                   // listed columns per step of a wavefront
+constexpr int kMChunk = 512;                   // listed columns staged at a time
+constexpr int kMAhead = 2;                     // sets requested ahead of the one that is multiplied
+constexpr int kMaxRows = 8;
 
 // The power of two that brings a row's largest |activation| (given as its bit pattern) into
 // [8, 16); 1 for an all-zero row.  Denormal and near-overflow maxima are clamped to factors
@@ -409,9 +428,32 @@ __device__ __forceinline__ float row_scale_up(uint32_t max_bits) {
     return __uint_as_float((uint32_t)up << 23);
 }
 
-__global__ __launch_bounds__(kMWaves * 64) void bgemv_q4_mfma_kernel(BatchedGemvParams p) {
-    __shared__ float red[kMGroups][8][8][16];    // [group][code position][batch row][lane column]
-    __shared__ float red1[kMGroups][8];          // sum of m*scale per (group, batch row)
+// Two fp16 numbers 1024 + (q + 8) 16^e, given as bits, and what takes them to q 16^e (exactly)
+typedef _Float16 h2_t __attribute__((ext_vector_type(2)));
+__device__ __forceinline__ uint32_t signed_codes(uint32_t bits, float offset) {
+    return __builtin_bit_cast(uint32_t, __builtin_bit_cast(h2_t, bits) + h2_t{(_Float16)offset, (_Float16)offset});
+}
+
+template <int KW>
+struct MfmaShared {
+    static constexpr int kGroups = kMGroups * (kMWaves / KW);   // groups of a workgroup
+    struct Stage {
+        int32_t row[kMChunk];                          // stored row ...
+        uint32_t off[kMChunk];                         // ... and its byte offset
+        float m[kMaxRows][kMChunk + 4];                // multipliers (0 past the share)
+        uint16_t sc[kGroups][kMChunk + 8];             // fp16 scales
+    };
+    union {
+        Stage st;
+        float red[KW > 1 ? KW : 1][kMaxRows][KW > 1 ? kGroups * 128 : 1];   // sums of the wavefronts
+    };
+};
+
+template <int KW>
+__global__ __launch_bounds__(kMWaves * 64, 2) void bgemv_q4_mfma_kernel(BatchedGemvParams p) {
+    typedef MfmaShared<KW> SH;
+    constexpr int CW = kMWaves / KW, STRIP = kMWaveCols * CW;
+    __shared__ __align__(16) SH sh;
     const int tid = threadIdx.x, lane = tid & 63;
     const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
     const int r = lane >> 4, c = lane & 15;
@@ -424,173 +466,229 @@ __global__ __launch_bounds__(kMWaves * 64) void bgemv_q4_mfma_kernel(BatchedGemv
     const float* uval = p.uval + layer * p.list_layer_stride * B;
     const uint32_t* rowmax = p.rowmax + 8 * layer;
     const uint16_t* scales = p.layer[layer].scales;
+    const char* wbytes = static_cast<const char*>(p.layer[layer].w);
+    const uint32_t row_stride = (uint32_t)p.row_stride;
     const int k = min((int)p.k_dev[layer], p.k_max);
     const int share = ((k + G - 1) / G + kMRowSet - 1) / kMRowSet * kMRowSet;
     const int kb = min(k, g * share), ke = min(k, kb + share);
 
-    f4_t acc[kMGroups][8], acc1[kMGroups];
+    f4_t acc[kMGroups][8];
 #pragma unroll
-    for (int gg = 0; gg < kMGroups; ++gg) {
-        acc1[gg] = f4_t{0.f, 0.f, 0.f, 0.f};
+    for (int gg = 0; gg < kMGroups; ++gg)
 #pragma unroll
         for (int t = 0; t < 8; ++t) acc[gg][t] = f4_t{0.f, 0.f, 0.f, 0.f};
-    }
-    // a ragged last strip has one group only: the second is re-read from the first and dropped
-    int grp[kMGroups];
-#pragma unroll
-    for (int gg = 0; gg < kMGroups; ++gg) grp[gg] = min(strip * kMGroups + gg, ngroups - 1);
-    const h4_t ones = {(_Float16)1.f, (_Float16)1.f, (_Float16)1.f, (_Float16)1.f};
-    const bool row_live = c < B;
 
-    // One set of 16 listed columns per step; the index vector of the next set is requested
-    // before the current one is multiplied.  Nothing branches on a lane: positions past the
-    // share read stored row 0 and are masked out of the left operand.  Offsets are 32-bit
-    // (a stored matrix is far below 4 GB) on top of scalar base pointers.
-    constexpr int STEP = kMWaves * kMRowSet;
-    // (the lists carry 16 spare entries past k_max, so whole index vectors may be read there)
-    auto load_idx = [&](int t) {
-        return *reinterpret_cast<const int4*>(uidx + min(t, p.k_max) + 4 * r);
+    // the wavefront's groups (past the right edge: the last one again, dropped at the end)
+    const int cw = wave % CW, kw = wave / CW;                // place along the columns, along the list
+    const int gslot = cw * kMGroups;                         // ... within the workgroup
+    const int g0 = strip * SH::kGroups + gslot;
+    const uint32_t wcol = (uint32_t)(min(g0 + (c >> 3), ngroups - 1) * 64 + 8 * (c & 7));
+    // this lane's row of the left operand: batch row c % 8, first term (c < 8) or 2^10 * second
+    const int b_lane = min(c & 7, B - 1);
+    const bool second = c >= 8;
+    const float m_scale = row_scale_up(rowmax[b_lane]) * (second ? 1024.0f : 1.0f);
+    const float whole = second ? 1.0f : 0.0f;
+
+    struct Codes { u32x2 q[8]; };
+    auto request = [&](int t, Codes& x) {
+        const uint4 o0 = *reinterpret_cast<const uint4*>(&sh.st.off[t + 8 * r]);
+        const uint4 o1 = *reinterpret_cast<const uint4*>(&sh.st.off[t + 8 * r + 4]);
+        const uint32_t off[8] = {o0.x, o0.y, o0.z, o0.w, o1.x, o1.y, o1.z, o1.w};
+#pragma unroll
+        for (int i = 0; i < 8; ++i)
+            x.q[i] = __builtin_nontemporal_load(reinterpret_cast<const u32x2*>(wbytes + (off[i] + wcol)));
     };
-    const char* wbytes = static_cast<const char*>(p.layer[layer].w);
-    const uint32_t row_stride = (uint32_t)p.row_stride;
-    const uint32_t wcol[kMGroups] = {(uint32_t)(grp[0] * 64 + 4 * c), (uint32_t)(grp[1] * 64 + 4 * c)};
-    const uint32_t cb = (uint32_t)min(c, B - 1);
-    const float row_up = row_scale_up(rowmax[cb]);     // this lane's batch row, into [8, 16)
-    int4 rn = load_idx(kb + wave * kMRowSet);
-    for (int t0 = kb + wave * kMRowSet; t0 < ke; t0 += STEP) {
-        const int rows[4] = {rn.x, rn.y, rn.z, rn.w};
-        rn = load_idx(t0 + STEP);
-        uint32_t wq[kMGroups][4];
-        uint16_t sc[kMGroups][4];
-        float mv[4];
-        uint32_t keep[2] = {0u, 0u};    // bit masks over the two fp16 pairs of the left operand
+    auto multiply = [&](int t, const Codes& x) {
+        const float4 m0 = *reinterpret_cast<const float4*>(&sh.st.m[b_lane][t + 8 * r]);
+        const float4 m1 = *reinterpret_cast<const float4*>(&sh.st.m[b_lane][t + 8 * r + 4]);
+        const float m[8] = {m0.x, m0.y, m0.z, m0.w, m1.x, m1.y, m1.z, m1.w};
+        float ms[8];
 #pragma unroll
-        for (int i = 0; i < 4; ++i) {
-            const int u = t0 + 4 * r + i;
-            const bool live = u < ke && (unsigned)rows[i] < (unsigned)p.n_in;
-            const uint32_t rr = live ? (uint32_t)rows[i] : 0u;
-            // entries past the share hold whatever the list memory held: they are masked out
-            // of the left operand bit-wise (never multiplied away), and the mask is plain
-            // arithmetic so that the load stays unconditional
-            mv[i] = uval[(uint32_t)min(u, p.k_max - 1) * (uint32_t)B + cb] * row_up;
-            if (live && row_live) keep[i >> 1] |= (i & 1) ? 0xffff0000u : 0x0000ffffu;
-            const uint32_t wrow = rr * row_stride;
-            const uint32_t srow = rr * (uint32_t)p.scale_stride;
-#pragma unroll
-            for (int gg = 0; gg < kMGroups; ++gg) {
-                wq[gg][i] = *reinterpret_cast<const uint32_t*>(wbytes + (wrow + wcol[gg]));
-                sc[gg][i] = scales[srow + (uint32_t)grp[gg]];
-            }
-        }
+        for (int i = 0; i < 8; ++i) ms[i] = m[i] * m_scale;
 #pragma unroll
         for (int gg = 0; gg < kMGroups; ++gg) {
-            float ms[4];
+            const h8_t sc = *reinterpret_cast<const h8_t*>(&sh.st.sc[gslot + gg][t + 8 * r]);
+            h8_t a;
 #pragma unroll
-            for (int i = 0; i < 4; ++i) {
-                _Float16 hs;
-                __builtin_memcpy(&hs, &sc[gg][i], 2);
-                ms[i] = mv[i] * (float)hs;
+            for (int i = 0; i < 8; ++i) {
+                const float v = fmaf(ms[i], (float)sc[i], 0.0f);     // (one v_fma_mix_f32)
+                const float top = __uint_as_float(__float_as_uint(v) & 0xffffe000u);
+                a[i] = (_Float16)fmaf(v, whole, -top);      // -top, or v - top
             }
-            // m * scale as a sum of two fp16 numbers: the rounded value and the rounded rest
-            // (a denormal, which the matrix cores keep): 22 significant bits instead of 11
-            _Float16 top[4], rest[4];
+            // the group's dwords of the 8 rows (see above)
+            uint32_t q[8];
 #pragma unroll
-            for (int i = 0; i < 4; ++i) {
-                top[i] = (_Float16)ms[i];
-                rest[i] = (_Float16)(ms[i] - (float)top[i]);
-            }
-            struct Pair { uint32_t lo, hi; };
-            Pair pa = __builtin_bit_cast(Pair, h4_t{top[0], top[1], top[2], top[3]});
-            Pair pb = __builtin_bit_cast(Pair, h4_t{rest[0], rest[1], rest[2], rest[3]});
-            pa.lo &= keep[0]; pa.hi &= keep[1];
-            pb.lo &= keep[0]; pb.hi &= keep[1];
-            const h4_t a = __builtin_bit_cast(h4_t, pa), a2 = __builtin_bit_cast(h4_t, pb);
-            uint32_t ev[4], od[4];
+            for (int i = 0; i < 8; ++i)
+                q[i] = (uint32_t)(gg == 0 ? __builtin_amdgcn_update_dpp((int)x.q[i].x, (int)x.q[i].y, 0x128, 0xf, 0xc, false)
+                                          : __builtin_amdgcn_update_dpp((int)x.q[i].y, (int)x.q[i].x, 0x128, 0xf, 0x3, false));
+            // pair (2i, 2i+1) of rows: the low (codes 0-3) or the high (codes 4-7) halves of their dwords
 #pragma unroll
-            for (int i = 0; i < 4; ++i) {
-                const uint32_t o = wq[gg][i] ^ 0x88888888u;     // q -> q + 8
-                ev[i] = o & 0x0f0f0f0fu;
-                od[i] = (o >> 4) & 0x0f0f0f0fu;
-                // keeps the byte extracts below from being narrowed into bit-field extracts
-                asm volatile("" : "+v"(ev[i]), "+v"(od[i]));
-            }
-#pragma unroll
-            for (int t = 0; t < 8; ++t) {
-                const int sh = 8 * (t >> 1);
-                float f[4];
-#pragma unroll
-                for (int i = 0; i < 4; ++i) f[i] = (float)((((t & 1) ? od[i] : ev[i]) >> sh) & 0xffu);
-                const h4_t codes = pack_h4(f[0], f[1], f[2], f[3]);
-                acc[gg][t] = __builtin_amdgcn_mfma_f32_16x16x16f16(a, codes, acc[gg][t], 0, 0, 0);
-                acc[gg][t] = __builtin_amdgcn_mfma_f32_16x16x16f16(a2, codes, acc[gg][t], 0, 0, 0);
-            }
-            acc1[gg] = __builtin_amdgcn_mfma_f32_16x16x16f16(a, ones, acc1[gg], 0, 0, 0);
-            acc1[gg] = __builtin_amdgcn_mfma_f32_16x16x16f16(a2, ones, acc1[gg], 0, 0, 0);
-        }
-    }
-    // A result register i of lane l is batch row 4 * (l / 16) + i, lane column l % 16: the
-    // first 32 lanes hold the 8 real rows.  One wavefront after the other adds its sums into
-    // the same LDS tile (fixed order).
-    for (int w = 0; w < kMWaves; ++w) {
-        if (wave == w && lane < 32) {
-#pragma unroll
-            for (int gg = 0; gg < kMGroups; ++gg) {
+            for (int half = 0; half < 2; ++half) {
+                u32x4 b[4];
 #pragma unroll
                 for (int i = 0; i < 4; ++i) {
-                    const int b = 4 * r + i;
-#pragma unroll
-                    for (int t = 0; t < 8; ++t) {
-                        float* dst = &red[gg][t][b][c];
-                        *dst = w == 0 ? acc[gg][t][i] : *dst + acc[gg][t][i];
-                    }
-                    if (c == 0) {
-                        float* dst = &red1[gg][b];
-                        *dst = w == 0 ? acc1[gg][i] : *dst + acc1[gg][i];
-                    }
+                    const uint32_t v = __builtin_amdgcn_perm(q[2 * i + 1], q[2 * i], half ? 0x07060302u : 0x05040100u);
+                    const uint32_t v8 = v >> 8;
+                    b[0][i] = signed_codes((v & 0x000f000fu) ^ 0x64086408u, -1032.0f);
+                    b[1][i] = signed_codes((v & 0x00f000f0u) ^ 0x64806480u, -1152.0f);
+                    b[2][i] = signed_codes((v8 & 0x000f000fu) ^ 0x64086408u, -1032.0f);
+                    b[3][i] = signed_codes((v8 & 0x00f000f0u) ^ 0x64806480u, -1152.0f);
                 }
+#pragma unroll
+                for (int tt = 0; tt < 4; ++tt)
+                    acc[gg][4 * half + tt] = __builtin_amdgcn_mfma_f32_16x16x32_f16(
+                        a, __builtin_bit_cast(h8_t, b[tt]), acc[gg][4 * half + tt], 0, 0, 0);
+            }
+        }
+    };
+
+    for (int c0 = kb; c0 < ke; c0 += kMChunk) {
+        // Stage the chunk, filled up with row 0 and zero multipliers.  Every thread requests all it
+        // stages before it waits for any of it (reads past the end are redirected and dropped).
+        constexpr int kThreads = kMWaves * 64;
+        const int n = min(ke - c0, kMChunk), n32 = (n + kMRowSet - 1) / kMRowSet * kMRowSet;
+        if (c0 > kb) __syncthreads();
+        {
+            constexpr int R = kMChunk / kThreads;
+            int row[R];
+            float m[R][kMaxRows];
+#pragma unroll
+            for (int j = 0; j < R; ++j) {
+                const int t = min(j * kThreads + tid, n - 1);
+                row[j] = uidx[c0 + t];
+#pragma unroll
+                for (int b = 0; b < kMaxRows; ++b) m[j][b] = uval[min(b, B - 1) * p.list_layer_stride + c0 + t];
+            }
+#pragma unroll
+            for (int j = 0; j < R; ++j) {
+                const int t = j * kThreads + tid;
+                const bool live = t < n && (unsigned)row[j] < (unsigned)p.n_in;
+                sh.st.row[t] = live ? row[j] : 0;
+                sh.st.off[t] = live ? (uint32_t)row[j] * row_stride : 0u;
+#pragma unroll
+                for (int b = 0; b < kMaxRows; ++b) sh.st.m[b][t] = live ? m[j][b] : 0.f;
             }
         }
         __syncthreads();
+        {
+            constexpr int E = kMChunk * SH::kGroups / kThreads, EB = E < 8 ? E : 8;
+            const int gs = tid % SH::kGroups, col = min(strip * SH::kGroups + gs, ngroups - 1);
+#pragma unroll
+            for (int e0 = 0; e0 < E; e0 += EB) {
+                uint16_t sc[EB];
+#pragma unroll
+                for (int j = 0; j < EB; ++j) {
+                    const int t = (tid + (e0 + j) * kThreads) / SH::kGroups;
+                    sc[j] = scales[(size_t)sh.st.row[t] * p.scale_stride + col];
+                }
+#pragma unroll
+                for (int j = 0; j < EB; ++j) sh.st.sc[gs][(tid + (e0 + j) * kThreads) / SH::kGroups] = sc[j];
+            }
+        }
+        __syncthreads();
+        // The codes of the next kMAhead sets are in flight while one is multiplied.  No request is
+        // under a branch -- past the end the last set is requested again and dropped -- since the
+        // wait behind a branch would be for all of them.
+        constexpr int STEP = KW * kMRowSet, RING = kMAhead + 1;
+        const int last = n32 - kMRowSet;
+        int t = kw * kMRowSet;
+        Codes x[RING];
+#pragma unroll
+        for (int s = 0; s < kMAhead; ++s) request(min(t + s * STEP, last), x[s]);
+        for (; t + kMAhead * STEP < n32; t += RING * STEP) {
+#pragma unroll
+            for (int s = 0; s < RING; ++s) {
+                request(min(t + (s + kMAhead) * STEP, last), x[(s + kMAhead) % RING]);
+                multiply(t + s * STEP, x[s]);
+            }
+        }
+#pragma unroll
+        for (int s = 0; s < kMAhead; ++s)
+            if (t + s * STEP < n32) multiply(t + s * STEP, x[s]);
     }
-    for (int o = tid; o < B * kMStripCols; o += kMWaves * 64) {
-        const int b = o / kMStripCols, cc = o % kMStripCols;
-        const int gcol = strip * kMStripCols + cc;
-        if (gcol >= p.n_out) continue;
-        const int gg = cc >> 7, cl = (cc & 127) >> 3, t = cc & 7;
-        const float row_down = 1.0f / row_scale_up(rowmax[b]);     // a power of two: exact
-        p.partial[layer * p.partial_layer_stride + ((size_t)g * B + b) * (size_t)p.n_out + gcol] = fmaf(-8.0f, red1[gg][b], red[gg][t][b][cl]) * row_down;
+
+    // Result register i of lane l is operand row 4 * (l / 16) + i, lane column l % 16: lanes 0-31
+    // hold the first terms of the 8 batch rows, lanes 32-63 the second ones.
+    if (KW > 1) __syncthreads();
+    const int col = c < 8 ? 16 * c : 16 * (c - 8) + 8;      // first of the lane's 8 columns of a group
+    auto join = [&](float v) { return __shfl_xor(v, 32) * (1.0f / 1024.0f) - v; };   // (for lanes 0-31)
+#pragma unroll
+    for (int gg = 0; gg < kMGroups; ++gg) {
+#pragma unroll
+        for (int i = 0; i < 4; ++i) {
+            const int b = 4 * r + i;                                   // (lanes 0-31)
+            float o[8];
+#pragma unroll
+            for (int t = 0; t < 8; ++t)
+                o[t] = join(acc[gg][t][i]) * ((t & 1) ? 0.0625f : 1.0f);
+            if (lane < 32 && b < B) {
+                if constexpr (KW > 1) {
+                    float4* dst = reinterpret_cast<float4*>(&sh.red[kw][b][(gslot + gg) * 128 + col]);
+                    dst[0] = make_float4(o[0], o[1], o[2], o[3]);
+                    dst[1] = make_float4(o[4], o[5], o[6], o[7]);
+                } else if (g0 + gg < ngroups) {
+                    const float down = 1.0f / row_scale_up(rowmax[b]);     // a power of two: exact
+                    float4* dst = reinterpret_cast<float4*>(p.partial + layer * p.partial_layer_stride +
+                                                            ((size_t)g * B + b) * (size_t)p.n_out + (g0 + gg) * 128 + col);
+                    dst[0] = make_float4(o[0] * down, o[1] * down, o[2] * down, o[3] * down);
+                    dst[1] = make_float4(o[4] * down, o[5] * down, o[6] * down, o[7] * down);
+                }
+            }
+        }
+    }
+    if constexpr (KW > 1) {
+        // the wavefronts' sums, added in order
+        __syncthreads();
+        for (int o = tid; o < B * STRIP; o += kMWaves * 64) {
+            const int b = o / STRIP, cc = o % STRIP;
+            const int gcol = strip * STRIP + cc;
+            if (gcol >= p.n_out) continue;
+            float s = 0.f;
+#pragma unroll
+            for (int w = 0; w < KW; ++w) s += sh.red[w][b][cc];
+            p.partial[layer * p.partial_layer_stride + ((size_t)g * B + b) * (size_t)p.n_out + gcol] =
+                s * (1.0f / row_scale_up(rowmax[b]));
+        }
     }
 }
 
 // out[b][j] = sum over shares of partial[g][b][j]   (glu == 0), or
 // out[b][j] = up * SiLU(gate), up = sum partial[g][b][j], gate = sum partial[g][b][half + j];
-// up to 20 shares in flight at a time (one or two memory round trips for the usual numbers
-// of shares), added in share order
-__global__ void breduce_kernel(BatchedReduceParams p) {
-    const int j = blockIdx.x * blockDim.x + threadIdx.x;
+// V outputs per lane, up to FLIGHT shares in flight at a time, added in share order.  Bound: the
+// reads of the sums; their number per lane is that of the shares (a fixed 20 in flight, the spare
+// ones re-reading the last share, took 49 us for two shares of 40 layers of the Phi-3-Medium
+// shape at 8 rows, where two in flight and 16 bytes per lane take 19 us).
+template <int V, int FLIGHT>
+__global__ __launch_bounds__(256) void breduce_kernel(BatchedReduceParams p) {
+    typedef float vec __attribute__((ext_vector_type(V)));
+    const int j = (blockIdx.x * 256 + threadIdx.x) * V;
     const int b = blockIdx.y;
     const int width = p.glu ? p.n_out / 2 : p.n_out;
     if (j >= width) return;
     const size_t gstride = (size_t)p.batch * (size_t)p.n_out;
     const float* src = p.partial + blockIdx.z * p.partial_layer_stride + (size_t)b * (size_t)p.n_out + j;
-    float s0 = 0.f, s1 = 0.f;
-    // (loads past the last share re-read it and are dropped: a load under a branch would be
-    //  waited for where the branch ends, one round trip each)
-    constexpr int kInFlight = 20;
-    const size_t goff = p.glu ? (size_t)width : 0;
-    for (int g0 = 0; g0 < p.shares; g0 += kInFlight) {
-        float a8[kInFlight], b8[kInFlight];
+    auto sum = [&](const float* q) {
+        vec s = vec(0.f);
+        for (int g0 = 0; g0 < p.shares; g0 += FLIGHT) {
+            vec a[FLIGHT];
+            // (loads past the last share re-read it and are dropped: a load under a branch would be
+            //  waited for where the branch ends, one round trip each)
 #pragma unroll
-        for (int i = 0; i < kInFlight; ++i) {
-            const int gg = g0 + i < p.shares ? g0 + i : p.shares - 1;
-            a8[i] = src[(size_t)gg * gstride];
-            b8[i] = src[(size_t)gg * gstride + goff];
+            for (int i = 0; i < FLIGHT; ++i)
+                a[i] = *reinterpret_cast<const vec*>(q + (size_t)min(g0 + i, p.shares - 1) * gstride);
+#pragma unroll
+            for (int i = 0; i < FLIGHT; ++i)
+                if (g0 + i < p.shares) s += a[i];
         }
+        return s;
+    };
+    vec s = sum(src);
+    if (p.glu) {
+        const vec gate = sum(src + width);
 #pragma unroll
-        for (int i = 0; i < kInFlight; ++i)
-            if (g0 + i < p.shares) { s0 += a8[i]; s1 += b8[i]; }
+        for (int v = 0; v < V; ++v) s[v] = s[v] * (gate[v] / (1.0f + expf(-gate[v])));
     }
-    p.out[blockIdx.z * p.out_layer_stride + (size_t)b * p.out_stride + j] = p.glu ? s0 * (s1 / (1.0f + expf(-s1))) : s0;
+    *reinterpret_cast<vec*>(p.out + blockIdx.z * p.out_layer_stride + (size_t)b * p.out_stride + j) = s;
 }
 
 template <int DT>
@@ -616,26 +714,42 @@ bool batched_on_matrix_cores(int dtype, int batch, int64_t n_in, int64_t row_str
     return dtype == DIP_INT4_G128 && batch >= kMfmaMinBatch && n_in * row_stride < ((int64_t)1 << 32);
 }
 
-int batched_strip_cols(int dtype, int batch, bool mc) {
-    if (mc) return kMStripCols;
-    (void)batch;
-    return dtype == DIP_F32 ? 16 * 4 : (dtype == DIP_BF16 ? 16 * 8 : 32 * 16);
+// Launch shape of the product: strip width, wavefronts of a workgroup along the list (matrix-core
+// product) and shares of the list.
+struct BatchedShape { int strip, kw, shares; };
+static BatchedShape batched_shape(int dtype, int n_out, int k_max, bool mc, int layers) {
+    if (!mc) {
+        // Vector-ALU product: about 1024 workgroups, at least 32 listed columns each.  Over several
+        // layers there are workgroups enough: shares of at most kLong listed columns keep the last
+        // round short, and every share costs a write and a read of its sums.
+        constexpr int kLong = 512;
+        const int sc = dtype == DIP_F32 ? 16 * 4 : (dtype == DIP_BF16 ? 16 * 8 : 32 * 16);
+        const int strips = (n_out + sc - 1) / sc * layers;
+        int g = (1024 + strips - 1) / strips;
+        if (layers > 1 && g < (k_max + kLong - 1) / kLong) g = (k_max + kLong - 1) / kLong;
+        while (g > 1 && k_max / g < 32) --g;
+        return {sc, 1, g < 1 ? 1 : g};
+    }
+    // Matrix-core product, two workgroups to a compute unit.  Wavefronts side by side stage the
+    // list once for 1024 stored columns and add nothing across wavefronts; taken where five rounds
+    // of such workgroups have a chunk of the list each or more.  Sums of more shares than that only
+    // cost: written between the reads of the codes, 230 MB of them (five shares at the
+    // Phi-3-Medium shape, 40 layers, 8 rows) take 85 of 444 us.
+    constexpr int kWide = kMWaves * kMWaveCols;
+    const int wide = (n_out + kWide - 1) / kWide * layers;
+    int g = (5 * 512 + wide - 1) / wide;
+    while (g > 1 && k_max / g < kMChunk) --g;
+    if ((int64_t)wide * g >= 1024) return {kWide, 1, g};
+    // One round of workgroups whose wavefronts take the sets of a narrow strip in turn, at least
+    // one set of 32 per wavefront.
+    const int strips = (n_out + kMWaveCols - 1) / kMWaveCols * layers;
+    g = 512 / strips;
+    while (g > 1 && k_max / g < kMWaves * kMRowSet) --g;
+    return {kMWaveCols, kMWaves, g < 1 ? 1 : g};
 }
 
-int batched_shares(int dtype, int batch, int n_out, int k_max, bool mc, int layers) {
-    // Vector-ALU product: about 1024 workgroups, at least 32 listed columns each.
-    // Matrix-core product: one round of workgroups -- three of them fit a compute unit, 768
-    // in all; 840 take as long as 1536 -- and at least one set of 16 per wavefront.
-    // Over several layers there are workgroups enough: shares of at most kLong listed columns
-    // keep the last round short, and every share costs a write and a read of its sums.
-    const int sc = batched_strip_cols(dtype, batch, mc);
-    const int strips = (n_out + sc - 1) / sc * layers;
-    const int min_rows = mc ? kMWaves * kMRowSet : 32;
-    const int kLong = mc ? 2048 : 512;
-    int g = mc ? 768 / strips : (1024 + strips - 1) / strips;
-    if (layers > 1 && g < (k_max + kLong - 1) / kLong) g = (k_max + kLong - 1) / kLong;
-    while (g > 1 && k_max / g < min_rows) --g;
-    return g < 1 ? 1 : g;
+int batched_shares(int dtype, int n_out, int k_max, bool mc, int layers) {
+    return batched_shape(dtype, n_out, k_max, mc, layers).shares;
 }
 
 hipError_t launch_union(const UnionParams& p, int layers, hipStream_t stream) {
@@ -647,13 +761,15 @@ hipError_t launch_union(const UnionParams& p, int layers, hipStream_t stream) {
 
 hipError_t launch_batched_gemv(const BatchedGemvParams& p, int shares, bool mc, int layers, hipStream_t stream,
                                int pk) {
-    const int sc = batched_strip_cols(p.dtype, p.batch, mc);
-    dim3 grid((p.n_out + sc - 1) / sc, shares, layers);
+    const BatchedShape shape = batched_shape(p.dtype, p.n_out, p.k_max, mc, layers);
+    dim3 grid((p.n_out + shape.strip - 1) / shape.strip, shares, layers);
     if (layers < 1 || layers > kStackLayers) return hipErrorInvalidValue;
     if (mc) {
         if (!p.rowmax || p.dtype != DIP_INT4_G128 || (int64_t)p.n_in * p.row_stride >= ((int64_t)1 << 32))
             return hipErrorInvalidValue;
-        return launch_timed(bgemv_q4_mfma_kernel, grid, dim3(kMWaves * 64), stream, pk, p);
+        const dim3 block(kMWaves * 64);
+        if (shape.kw == 1) return launch_timed(bgemv_q4_mfma_kernel<1>, grid, block, stream, pk, p);
+        return launch_timed(bgemv_q4_mfma_kernel<kMWaves>, grid, block, stream, pk, p);
     }
     if (p.dtype == DIP_F32) return launch_dt<DIP_F32>(p, grid, stream, pk);
     if (p.dtype == DIP_BF16) return launch_dt<DIP_BF16>(p, grid, stream, pk);
@@ -661,10 +777,25 @@ hipError_t launch_batched_gemv(const BatchedGemvParams& p, int shares, bool mc, 
     return hipErrorInvalidValue;
 }
 
-hipError_t launch_batched_reduce(const BatchedReduceParams& p, int layers, hipStream_t stream) {
+template <int V>
+static hipError_t launch_reduce(const BatchedReduceParams& p, int layers, hipStream_t stream) {
     const int width = p.glu ? p.n_out / 2 : p.n_out;
-    hipLaunchKernelGGL(breduce_kernel, dim3((width + 255) / 256, p.batch, layers), dim3(256), 0, stream, p);
+    const dim3 grid((width + 256 * V - 1) / (256 * V), p.batch, layers), block(256);
+    if (p.shares <= 2) hipLaunchKernelGGL((breduce_kernel<V, 2>), grid, block, 0, stream, p);
+    else if (p.shares <= 6) hipLaunchKernelGGL((breduce_kernel<V, 6>), grid, block, 0, stream, p);
+    else hipLaunchKernelGGL((breduce_kernel<V, 20>), grid, block, 0, stream, p);
     return hipGetLastError();
+}
+
+hipError_t launch_batched_reduce(const BatchedReduceParams& p, int layers, hipStream_t stream) {
+    // 16 bytes per lane where every row of sums and outputs starts on 16 bytes and that still makes
+    // a workgroup for every second compute unit; a single layer wants the lanes instead
+    const int width = p.glu ? p.n_out / 2 : p.n_out;
+    const bool vec = width % 4 == 0 && p.n_out % 4 == 0 && p.partial_layer_stride % 4 == 0 && p.out_stride % 4 == 0 &&
+                     p.out_layer_stride % 4 == 0 &&
+                     ((reinterpret_cast<uintptr_t>(p.partial) | reinterpret_cast<uintptr_t>(p.out)) & 15) == 0 &&
+                     (int64_t)width * p.batch * layers >= 128 * 1024;
+    return vec ? launch_reduce<4>(p, layers, stream) : launch_reduce<1>(p, layers, stream);
 }
 
 }  // namespace dip

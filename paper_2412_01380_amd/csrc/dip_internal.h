@@ -238,7 +238,8 @@ struct UnionParams {
     uint32_t* union_words;     // ceil(n/32)
     int64_t union_layer_stride;
     int32_t* uidx;             // ascending indices of the union, up to min(n, batch*k)
-    float* uval;               // [listed][batch]: x[b][i] if row b selected i, else 0
+    float* uval;               // x[b][i] if row b selected i, else 0, as [listed][batch] or ...
+    int row_major;             // ... 1: [batch][list_layer_stride] (the matrix-core product)
     int64_t list_layer_stride; // entries (uval: times batch)
     uint32_t* count_out;       // number of listed indices, one word per layer
 };
@@ -249,7 +250,7 @@ struct BatchedGemvParams {
     int n_in;
     int n_out;                 // full stored row width
     const int32_t* uidx;
-    const float* uval;
+    const float* uval;         // as UnionParams wrote it
     int64_t list_layer_stride;
     const uint32_t* k_dev;     // listed columns (device), one word per layer
     int k_max;                 // capacity of the lists
@@ -275,8 +276,7 @@ struct BatchedReduceParams {
     int64_t out_layer_stride;
 };
 bool batched_on_matrix_cores(int dtype, int batch, int64_t n_in, int64_t row_stride);
-int batched_strip_cols(int dtype, int batch, bool mc);
-int batched_shares(int dtype, int batch, int n_out, int k_max, bool mc, int layers);
+int batched_shares(int dtype, int n_out, int k_max, bool mc, int layers);
 hipError_t launch_union(const UnionParams& p, int layers, hipStream_t stream);
 hipError_t launch_batched_gemv(const BatchedGemvParams& p, int shares, bool mc, int layers, hipStream_t stream,
                                int prof_kind);

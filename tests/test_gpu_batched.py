@@ -223,3 +223,31 @@ def test_batched_stack_in_phases_matches_per_layer_calls(D, fmt, B):
             assert rel_l2(Y[l].cpu().numpy(), Y1.cpu().numpy()) <= tol, (t, l)
             for a, b in ((caches[0][l], caches[2][l]), (caches[1][l], caches[3][l])):
                 assert torch.equal(a.bits, b.bits) and torch.equal(a.stamp, b.stamp) and torch.equal(a.meta, b.meta), (t, l)
+
+
+@pytest.mark.parametrize("B", [3, 8])
+def test_batched_int4_stack_wide_workgroups(D, B):
+    """Many layers of one shape: the matrix-core product runs with its wavefronts side by side
+    (strips of 1024 stored columns, here ragged ones: 66 and 9 groups), the list staged in chunks of
+    512, with union sizes from one column to all at the edges of sets, chunks and shares.  The
+    one-layer calls split the same terms over other workgroups: only the order of the fp32 sums
+    differs (a few 1e-7)."""
+    d, f, L = 1152, 4224, 64
+    w = layer_weights(d, f, seed=64, layer=0, dtype="int4")
+    mlp = D.Mlp(make_weight(D, w["ug"]), make_weight(D, w["d"]))
+    k_in = [d] * L
+    k_in[:8] = [1, 31, 32, 33, 170, 191, 200, 400]
+    k_mid = [f] * L
+    k_mid[8:16] = [1, 31, 33, 64, 171, 512, 513, 1409]
+    stack = D.MlpStack([mlp] * L)
+    ws = workspace(D.dip_swiglu_mlp_forward_batched_stack_workspace_bytes(stack, B, k_in, k_mid))
+    ws.fill_(0xFF)        # nothing is expected of the workspace's contents
+    X = dev_f32(np.stack([ar1_laplace_stream(1, d, seed=800 + i)[0] for i in range(L * B)]).reshape(L, B, d))
+    Y = torch.full((L, B, d), float("nan"), device="cuda")
+    D.dip_swiglu_mlp_forward_batched_stack(stack, X, B * d, B, k_in, k_mid, 0.2, Y, B * d, ws)
+    Y1 = torch.empty(B, d, dtype=torch.float32, device="cuda")
+    for l in range(L):
+        one = workspace(D.dip_swiglu_mlp_forward_batched_workspace_bytes(mlp, B, k_in[l], k_mid[l]))
+        D.dip_swiglu_mlp_forward_batched(mlp, X[l], B, k_in[l], k_mid[l], None, None, 0.2, Y1, None, None, None, one)
+        torch.cuda.synchronize()
+        assert rel_l2(Y[l].cpu().numpy(), Y1.cpu().numpy()) <= 4e-6, (l, k_in[l], k_mid[l])
