@@ -95,14 +95,13 @@ int32_t validate_gamma(float gamma) {
 // [ mask words of every layer: point 1, point 2 ]  kept until the cache updates at the end of the call
 // [ scratch of one layer, shared by all layers   ]  index lists, h~, partial sums, ticket counters
 constexpr size_t kMaskBytes = sizeof(uint32_t) * (DIP_MAX_N / 32);
-constexpr int kMaxCounters = 2048;   // strips of the two products of a layer, at the narrowest strip width
+constexpr int kMaxCounters = 1024;   // strips of a product, at the narrowest strip width
 
 struct ForwardPlan {
     int d, f;
     GemvShape ug, dn;          // selection and product launched apart
     GemvShape fug, fdn;        // product with the selection at its head
     bool fuse_ug, fuse_dn;
-    int strips_ug, strips_dn;  // ticket counters (the larger of the two launch shapes)
     size_t off_idx1, off_val1, off_h, off_idx2, off_val2, off_part_ug, off_part_dn, off_cnt;
     size_t total;              // scratch of the layer, without the mask words
 };
@@ -115,22 +114,13 @@ ForwardPlan plan_forward(const dip_mlp* mlp, int k_in, int k_mid) {
     pl.dn = choose_gemv_shape(mlp->w_d.dtype, pl.d, 1, k_mid);
     pl.fuse_ug = fused_shape(mlp->w_ug.dtype, pl.d, pl.f, 2, k_in, &pl.fug);
     pl.fuse_dn = fused_shape(mlp->w_d.dtype, pl.f, pl.d, 1, k_mid, &pl.fdn);
-    pl.strips_ug = gemv_strips(pl.ug, mlp->w_ug.dtype, pl.f);
-    pl.strips_dn = gemv_strips(pl.dn, mlp->w_d.dtype, pl.d);
     int ks_ug = pl.ug.ksplit, ks_dn = pl.dn.ksplit;
-    if (pl.fuse_ug) {
-        pl.strips_ug = std::max(pl.strips_ug, gemv_strips(pl.fug, mlp->w_ug.dtype, pl.f));
-        ks_ug = std::max(ks_ug, pl.fug.ksplit);
-    }
-    if (pl.fuse_dn) {
-        pl.strips_dn = std::max(pl.strips_dn, gemv_strips(pl.fdn, mlp->w_d.dtype, pl.d));
-        ks_dn = std::max(ks_dn, pl.fdn.ksplit);
-    }
+    if (pl.fuse_ug) ks_ug = std::max(ks_ug, pl.fug.ksplit);
+    if (pl.fuse_dn) ks_dn = std::max(ks_dn, pl.fdn.ksplit);
     size_t o = 0;
     auto take = [&](size_t bytes) { size_t at = o; o = align_up(o + bytes, 256); return at; };
-    // the ticket counters come first: they sit at the same place for every layer shape, are
-    // cleared once per call and return to zero with every launch that uses them
-    pl.off_cnt = take(sizeof(uint32_t) * kMaxCounters);
+    // ticket counters, the same for both products (a launch tells its own tickets by their tag)
+    pl.off_cnt = take(sizeof(uint64_t) * kMaxCounters);
     pl.off_idx1 = take(sizeof(int32_t) * k_in);
     pl.off_val1 = take(sizeof(float) * k_in);
     pl.off_h = take(sizeof(float) * pl.f);
@@ -187,8 +177,7 @@ int32_t forward_one(const dip_mlp* mlp, const ForwardPlan& pl, const float* x, i
     float* val2 = reinterpret_cast<float*>(ws + pl.off_val2);
     float* part_ug = reinterpret_cast<float*>(ws + pl.off_part_ug);
     float* part_dn = reinterpret_cast<float*>(ws + pl.off_part_dn);
-    uint32_t* cnt_ug = reinterpret_cast<uint32_t*>(ws + pl.off_cnt);
-    uint32_t* cnt_dn = cnt_ug + pl.strips_ug;
+    uint64_t* counters = reinterpret_cast<uint64_t*>(ws + pl.off_cnt);
     if (dbg && dbg->idx_in) idx1 = dbg->idx_in;
     if (dbg && dbg->idx_mid) idx2 = dbg->idx_mid;
     if (dbg && dbg->h) h = dbg->h;
@@ -203,7 +192,7 @@ int32_t forward_one(const dip_mlp* mlp, const ForwardPlan& pl, const float* x, i
     g1.w = mlp->w_ug.data; g1.row_stride = mlp->w_ug.row_stride_bytes;
     g1.scales = static_cast<const uint16_t*>(mlp->w_ug.scales); g1.scale_stride = mlp->w_ug.n_out / 128; g1.dtype = mlp->w_ug.dtype;
     g1.n_in = pl.d; g1.n_out = pl.f; g1.nseg = 2; g1.k = k_in; g1.out = h;
-    g1.partial = part_ug; g1.counters = cnt_ug;
+    g1.partial = part_ug; g1.counters = counters;
     if (dense_in) {
         // GLU pruning (Sec. 3.2): nothing is pruned at point 1, every stored row in order
         // (in the launch shape DIP would use with k_in = d_model, so that both give the same bits)
@@ -238,7 +227,7 @@ int32_t forward_one(const dip_mlp* mlp, const ForwardPlan& pl, const float* x, i
     g2.w = mlp->w_d.data; g2.row_stride = mlp->w_d.row_stride_bytes;
     g2.scales = static_cast<const uint16_t*>(mlp->w_d.scales); g2.scale_stride = mlp->w_d.n_out / 128; g2.dtype = mlp->w_d.dtype;
     g2.n_in = pl.f; g2.n_out = pl.d; g2.nseg = 1; g2.k = k_mid; g2.out = y;
-    g2.partial = part_dn; g2.counters = cnt_dn;
+    g2.partial = part_dn; g2.counters = counters;
     if (pl.fuse_dn) {
         FusedParams fp;
         fp.g = g2;
@@ -519,7 +508,7 @@ size_t dip_gathered_gemv_workspace_bytes(const dip_weight* w, int32_t k) {
     if (w->dtype != DIP_F32 && w->dtype != DIP_BF16 && w->dtype != DIP_INT4_G128) return 0;
     const GemvShape s = choose_gemv_shape(w->dtype, w->n_out, 1, k);
     const int strips = gemv_strips(s, w->dtype, w->n_out);
-    size_t bytes = align_up(sizeof(uint32_t) * strips, 256);
+    size_t bytes = align_up(sizeof(uint64_t) * strips, 256);
     bytes += 2 * align_up(sizeof(float) * (size_t)k, 256);   // aligned copies of idx and x[idx]
     if (s.ksplit > 1) bytes += align_up(sizeof(float) * (size_t)w->n_out * s.ksplit, 256);
     return bytes;
@@ -538,26 +527,30 @@ int32_t dip_gathered_gemv(const dip_weight* w, const float* x, const int32_t* id
     const int strips = gemv_strips(s, w->dtype, w->n_out);
     hipStream_t hs = static_cast<hipStream_t>(stream);
     char* base = static_cast<char*>(ws);
-    uint32_t* counters = reinterpret_cast<uint32_t*>(base);
-    size_t o = align_up(sizeof(uint32_t) * strips, 256);
+    uint64_t* counters = reinterpret_cast<uint64_t*>(base);
+    size_t o = align_up(sizeof(uint64_t) * strips, 256);
     int32_t* idx_copy = reinterpret_cast<int32_t*>(base + o);
     o += align_up(sizeof(float) * (size_t)k, 256);
     float* val = reinterpret_cast<float*>(base + o);
     o += align_up(sizeof(float) * (size_t)k, 256);
     float* partial = reinterpret_cast<float*>(base + o);
-    if (s.ksplit > 1) {
-        st = check_hip(launch_zero_u32(counters, strips, hs), "dip_gathered_gemv: counter reset");
-        if (st) return st;
-    }
-    // the kernel reads (index, multiplier) pairs as aligned vectors
-    st = check_hip(launch_gather(x, idx, k, w->n_in, val, idx_copy, hs), "dip_gathered_gemv: gather");
-    if (st) return st;
     GemvParams p;
     std::memset(&p, 0, sizeof(p));
     p.w = w->data; p.row_stride = w->row_stride_bytes; p.dtype = w->dtype;
     p.scales = static_cast<const uint16_t*>(w->scales); p.scale_stride = w->n_out / 128; p.n_in = w->n_in; p.n_out = w->n_out;
-    p.nseg = 1; p.idx = idx_copy; p.val = val; p.k = k; p.out = y_out;
+    p.nseg = 1; p.idx = idx; p.k = k; p.out = y_out;
     p.partial = partial; p.counters = counters;
+    // (an output over x or idx: they must be read before any workgroup writes)
+    auto apart = [&](const void* q, size_t bytes) {
+        const uintptr_t a = reinterpret_cast<uintptr_t>(q), b = reinterpret_cast<uintptr_t>(y_out);
+        return a + bytes <= b || b + sizeof(float) * (size_t)w->n_out <= a;
+    };
+    if (gather_in_gemv(s, k) && apart(x, sizeof(float) * (size_t)w->n_in) && apart(idx, sizeof(int32_t) * (size_t)k))
+        return check_hip(launch_gemv_gather(p, x, s, hs, DIP_KERNEL_GEMV_DOWN), "dip_gathered_gemv");
+    // the kernel reads (index, multiplier) pairs as aligned vectors
+    st = check_hip(launch_gather(x, idx, k, w->n_in, val, idx_copy, hs), "dip_gathered_gemv: gather");
+    if (st) return st;
+    p.idx = idx_copy; p.val = val;
     return check_hip(launch_gemv(p, s, hs, DIP_KERNEL_GEMV_DOWN), "dip_gathered_gemv");
 }
 
@@ -628,7 +621,6 @@ static int32_t forward_checked(const dip_mlp* mlps, int32_t n_layers, const floa
     updates.reserve(2 * (size_t)n_layers);
     const bool phases = n_layers >= kMinStackLayers && !dbg && !dense_in && g_fusion && !tuned() &&
                         !stack_chained(mlps, n_layers, 1, x, x_stride, y_out, y_stride);
-    bool counters_zero = false;
     for (int l = 0, m; l < n_layers && !st; l += m) {
         m = phases ? stack_group(mlps, n_layers, l) : 1;
         if (m >= kMinStackLayers) {
@@ -636,16 +628,9 @@ static int32_t forward_checked(const dip_mlp* mlps, int32_t n_layers, const floa
                                      k_mid + l * k_stride, k_stride, caches_in ? &caches_in[l] : nullptr,
                                      caches_mid ? &caches_mid[l] : nullptr, gamma, y_out + (int64_t)l * y_stride, y_stride,
                                      scratch, reinterpret_cast<uint32_t*>(base + (size_t)(2 * l) * kMaskBytes), hs, updates);
-            counters_zero = false;      // the scratch of the phases lies over the counters
             continue;
         }
         m = 1;
-        if (!counters_zero) {
-            // the ticket counters of the products start at zero and return to zero with every launch
-            st = check_hip(launch_zero_u32(reinterpret_cast<uint32_t*>(scratch), kMaxCounters, hs), "counter reset");
-            if (st) break;
-            counters_zero = true;
-        }
         const int ki = k_in[l * k_stride], km = k_mid[l * k_stride];
         const ForwardPlan pl = plan_forward(&mlps[l], ki, km);
         uint32_t* mask1 = reinterpret_cast<uint32_t*>(base + (size_t)(2 * l) * kMaskBytes);
@@ -1027,7 +1012,7 @@ PartialPlan plan_partial(const dip_mlp_split* mlp, int k) {
     pl.off_hsel = take(sizeof(float) * k);
     pl.off_part_dense = take(pl.dense.ksplit > 1 ? sizeof(float) * pl.f * pl.dense.ksplit : 0);
     pl.off_part_dn = take(pl.dn.ksplit > 1 ? sizeof(float) * pl.d * pl.dn.ksplit : 0);
-    pl.off_cnt = take(sizeof(uint32_t) * (pl.strips_dense + pl.strips_dn));
+    pl.off_cnt = take(sizeof(uint64_t) * std::max(pl.strips_dense, pl.strips_dn));
     pl.total = o;
     return pl;
 }
@@ -1074,11 +1059,7 @@ int32_t dip_partial_pruning_forward(const dip_mlp_split* mlp, int32_t scheme, co
     float* a = dbg && dbg->a ? dbg->a : reinterpret_cast<float*>(base + pl.off_a);
     int32_t* idx = dbg && dbg->idx ? dbg->idx : reinterpret_cast<int32_t*>(base + pl.off_idx);
     float* hsel = dbg && dbg->h_sel ? dbg->h_sel : reinterpret_cast<float*>(base + pl.off_hsel);
-    uint32_t* cnt_dense = reinterpret_cast<uint32_t*>(base + pl.off_cnt);
-    uint32_t* cnt_dn = cnt_dense + pl.strips_dense;
-
-    st = check_hip(launch_zero_u32(cnt_dense, pl.strips_dense + pl.strips_dn, hs), "counter reset");
-    if (st) return st;
+    uint64_t* counters = reinterpret_cast<uint64_t*>(base + pl.off_cnt);
 
     // a = sigma(W^g x) (gate pruning) or W^u x (up pruning), all d_ff neurons
     GemvParams g1;
@@ -1087,7 +1068,7 @@ int32_t dip_partial_pruning_forward(const dip_mlp_split* mlp, int32_t scheme, co
     g1.scales = static_cast<const uint16_t*>(mlp->w_dense.scales); g1.scale_stride = mlp->w_dense.n_out / 128;
     g1.dtype = mlp->w_dense.dtype; g1.n_in = pl.d; g1.n_out = pl.f; g1.nseg = 1;
     g1.idx = nullptr; g1.val = x; g1.k = pl.d; g1.out = a;
-    g1.partial = reinterpret_cast<float*>(base + pl.off_part_dense); g1.counters = cnt_dense;
+    g1.partial = reinterpret_cast<float*>(base + pl.off_part_dense); g1.counters = counters;
     g1.act = scheme == DIP_GATE_PRUNING ? 1 : 0;
     st = check_hip(launch_gemv(g1, pl.dense, hs, DIP_KERNEL_GEMV_DENSE), "dense GEMV");
     if (st) return st;
@@ -1116,7 +1097,7 @@ int32_t dip_partial_pruning_forward(const dip_mlp_split* mlp, int32_t scheme, co
     g2.scales = static_cast<const uint16_t*>(mlp->w_d.scales); g2.scale_stride = mlp->w_d.n_out / 128;
     g2.dtype = mlp->w_d.dtype; g2.n_in = pl.f; g2.n_out = pl.d; g2.nseg = 1;
     g2.idx = idx; g2.val = hsel; g2.k = k; g2.out = y_out;
-    g2.partial = reinterpret_cast<float*>(base + pl.off_part_dn); g2.counters = cnt_dn;
+    g2.partial = reinterpret_cast<float*>(base + pl.off_part_dn); g2.counters = counters;
     return check_hip(launch_gemv(g2, pl.dn, hs, DIP_KERNEL_GEMV_DOWN), "gathered GEMV (down)");
 }
 
@@ -1230,8 +1211,7 @@ int32_t dip_tiered_mlp_forward(const dip_tiered_mlp* mlp, const float* x, int32_
     if (dbg && dbg->idx_in) idx[0] = dbg->idx_in;
     if (dbg && dbg->idx_mid) idx[1] = dbg->idx_mid;
     if (dbg && dbg->h) h = dbg->h;
-    uint32_t* cnt_ug = reinterpret_cast<uint32_t*>(base + pl.off_cnt);
-    uint32_t* cnt_dn = cnt_ug + pl.strips_ug;
+    uint64_t* counters = reinterpret_cast<uint64_t*>(base + pl.off_cnt);
 
     for (int pt = 0; pt < 2; ++pt) {
         const dip_tiered_weight& tw = pt == 0 ? mlp->w_ug : mlp->w_d;
@@ -1255,7 +1235,6 @@ int32_t dip_tiered_mlp_forward(const dip_tiered_mlp* mlp, const float* x, int32_
         sp.score_bits = cache->bits; sp.c_bits = cache->bits; sp.c_stamp = cache->stamp; sp.c_meta = cache->meta;
         sp.capacity = cache->capacity; sp.policy = cache->policy;
         sp.evicted_out = evw; sp.inserted_out = insw;
-        if (pt == 0) { sp.zero_ptr = cnt_ug; sp.zero_n = pl.strips_ug + pl.strips_dn; }
         if ((st = check_hip(launch_select(sp, hs, pt == 0 ? DIP_KERNEL_SELECT_IN : DIP_KERNEL_SELECT_MID), "select"))) return st;
 
         // slots for the inserted columns, rows to copy, rows to read
@@ -1278,12 +1257,12 @@ int32_t dip_tiered_mlp_forward(const dip_tiered_mlp* mlp, const float* x, int32_
         g.idx = src; g.val = val[pt]; g.k = k;
         if (pt == 0) {
             g.n_out = pl.f; g.nseg = 2; g.out = h;
-            g.partial = reinterpret_cast<float*>(base + pl.off_part_ug); g.counters = cnt_ug;
+            g.partial = reinterpret_cast<float*>(base + pl.off_part_ug); g.counters = counters;
             // (the launch shapes of dip_swiglu_mlp_forward: the same sums in the same order)
             st = check_hip(launch_gemv(g, pl.fuse_ug ? pl.fug : pl.ug, hs, DIP_KERNEL_GEMV_UPGATE), "gathered GEMV (up/gate)");
         } else {
             g.n_out = pl.d; g.nseg = 1; g.out = y_out;
-            g.partial = reinterpret_cast<float*>(base + pl.off_part_dn); g.counters = cnt_dn;
+            g.partial = reinterpret_cast<float*>(base + pl.off_part_dn); g.counters = counters;
             st = check_hip(launch_gemv(g, pl.fuse_dn ? pl.fdn : pl.dn, hs, DIP_KERNEL_GEMV_DOWN), "gathered GEMV (down)");
         }
         if (st) return st;

@@ -15,6 +15,11 @@
 // strip through a partial buffer that the last workgroup to arrive adds in index order.
 // The result is bit-repeatable for a given launch shape.
 
+#include <time.h>
+#include <unistd.h>
+
+#include <atomic>
+
 #include "dip_gemv_device.h"
 
 namespace dip {
@@ -36,9 +41,41 @@ __global__ __launch_bounds__(WAVES * 64) void gemv_kernel(GemvParams p) {
     // this workgroup's share of the selected rows
     const int kb = min(p.k, g * p.rows_per_split);   // rows_per_split is a multiple of 8
     const int ke = min(p.k, kb + p.rows_per_split);
+    const uint64_t seen = ticket_peek(p, strip, G);
     float acc[NSEG][T::EPL];
     accumulate<WT, LPR, WAVES, UNROLL, NSEG>(p, p.idx, p.val, 0, kb, ke, strip, acc);
-    finish<WT, LPR, WAVES, UNROLL, NSEG, true>(p, acc, strip, g, G, red, s_last);
+    ticket_open(p, strip, seen);
+    finish<WT, LPR, WAVES, UNROLL, NSEG>(p, acc, strip, g, G, red, s_last);
+}
+
+// The same in the default shape for a caller's own index list: the workgroup takes its share of the
+// list and the activations at it into LDS, where the row loop reads aligned vectors whatever the
+// caller's alignment.  (A launch in front that copied the list and gathered the activations took
+// as long as a third of the product: 2.4 us and the gap behind it, 4100 x 1229 in fp32.)
+constexpr int kGatherLpr = 16, kGatherWaves = 8, kGatherUnroll = 4;
+constexpr int kGatherCap = 2048;     // rows of a share: 16 KB of LDS
+template <typename WT>
+__global__ __launch_bounds__(kGatherWaves * 64) void gemv_gather_kernel(GemvParams p, const float* x) {
+    typedef Tile<WT, kGatherLpr, kGatherWaves, kGatherUnroll, 1> T;
+    __shared__ __align__(16) int32_t l_idx[kGatherCap];
+    __shared__ __align__(16) float l_val[kGatherCap];
+    __shared__ float red[kGatherWaves][1][T::SC];
+    __shared__ int s_last;
+    const int strip = blockIdx.x;
+    const int g = blockIdx.y, G = gridDim.y;
+    const int kb = min(p.k, g * p.rows_per_split);   // rows_per_split is a multiple of 8, <= kGatherCap
+    const int ke = min(p.k, kb + p.rows_per_split);
+    const uint64_t seen = ticket_peek(p, strip, G);
+    for (int t = threadIdx.x; t < ke - kb; t += kGatherWaves * 64) {
+        const int r = p.idx[kb + t];
+        l_idx[t] = r;
+        l_val[t] = (unsigned)r < (unsigned)p.n_in ? x[r] : 0.f;
+    }
+    ticket_open(p, strip, seen);
+    __syncthreads();
+    float acc[1][T::EPL];
+    accumulate<WT, kGatherLpr, kGatherWaves, kGatherUnroll, 1>(p, l_idx, l_val, kb, kb, ke, strip, acc);
+    finish<WT, kGatherLpr, kGatherWaves, kGatherUnroll, 1>(p, acc, strip, g, G, red, s_last);
 }
 
 // ---------------------------------------------------------------------------------------
@@ -396,6 +433,7 @@ bool fused_shape(int dtype, int n_sel, int n_out, int nseg, int k, GemvShape* sh
 
 hipError_t launch_fused(const FusedParams& p0, const GemvShape& s, hipStream_t stream, int pk) {
     FusedParams p = p0;
+    p.g.epoch = next_epoch();
     p.g.rows_per_split = ((p.g.k + s.ksplit - 1) / s.ksplit + 7) / 8 * 8;
     if (p.g.rows_per_split > kFusedListCap || s.waves != 16 || s.unroll != 4) return hipErrorInvalidConfiguration;
     if (p.s.n < 1 || p.s.n > DIP_MAX_N || p.g.k < 1 || p.g.k > p.s.n || p.s.n != p.g.n_in) return hipErrorInvalidValue;
@@ -415,12 +453,50 @@ hipError_t launch_fused(const FusedParams& p0, const GemvShape& s, hipStream_t s
     return hipErrorInvalidValue;
 }
 
+// The tags start at a point that differs from process to process (time and process, mixed by the
+// finaliser of splitmix64), so that words left in memory by another one do not match either.
+uint64_t next_epoch() {
+    static std::atomic<uint64_t> next{[] {
+        struct timespec t = {0, 0};
+        clock_gettime(CLOCK_REALTIME, &t);
+        uint64_t z = (uint64_t)t.tv_sec * 1000000000ull + (uint64_t)t.tv_nsec + ((uint64_t)getpid() << 40);
+        z = (z ^ (z >> 30)) * 0xbf58476d1ce4e5b9ull;
+        z = (z ^ (z >> 27)) * 0x94d049bb133111ebull;
+        return z ^ (z >> 31);
+    }()};
+    return next.fetch_add(1, std::memory_order_relaxed) << 16;
+}
+
 hipError_t launch_gemv(const GemvParams& p0, const GemvShape& s, hipStream_t stream, int pk) {
     GemvParams p = p0;
+    p.epoch = next_epoch();
     p.rows_per_split = ((p.k + s.ksplit - 1) / s.ksplit + 7) / 8 * 8;   // keeps vector index loads aligned
     if (p.dtype == DIP_F32) return launch_lpr<float>(p, s, stream, pk);
     if (p.dtype == DIP_BF16) return launch_lpr<uint16_t>(p, s, stream, pk);
     if (p.dtype == DIP_INT4_G128) return launch_lpr<q4n_t>(p, s, stream, pk);
+    return hipErrorInvalidValue;
+}
+
+bool gather_in_gemv(const GemvShape& s, int k) {
+    return s.lpr == kGatherLpr && s.waves == kGatherWaves && s.unroll == kGatherUnroll &&
+           ((k + s.ksplit - 1) / s.ksplit + 7) / 8 * 8 <= kGatherCap;
+}
+
+hipError_t launch_gemv_gather(const GemvParams& p0, const float* x, const GemvShape& s, hipStream_t stream, int pk) {
+    if (!gather_in_gemv(s, p0.k) || p0.nseg != 1 || p0.w_alt) return hipErrorInvalidValue;
+    GemvParams p = p0;
+    p.epoch = next_epoch();
+    p.rows_per_split = ((p.k + s.ksplit - 1) / s.ksplit + 7) / 8 * 8;
+    const dim3 grid(gemv_strips(s, p.dtype, p.n_out), s.ksplit), block(kGatherWaves * 64);
+    auto go = [&](auto kernel) {
+        hipEvent_t e0, e1;
+        if (pk >= 0 && prof_next(pk, &e0, &e1)) hipExtLaunchKernelGGL(kernel, grid, block, 0, stream, e0, e1, 0, p, x);
+        else hipLaunchKernelGGL(kernel, grid, block, 0, stream, p, x);
+        return hipGetLastError();
+    };
+    if (p.dtype == DIP_F32) return go(gemv_gather_kernel<float>);
+    if (p.dtype == DIP_BF16) return go(gemv_gather_kernel<uint16_t>);
+    if (p.dtype == DIP_INT4_G128) return go(gemv_gather_kernel<q4n_t>);
     return hipErrorInvalidValue;
 }
 

@@ -309,14 +309,31 @@ __device__ __forceinline__ void accumulate(const GemvParams& p, const int32_t* i
     }
 }
 
+// Ticket counters.  A counter word is the tag of a launch (upper 48 bits, different for every
+// launch of every call) and the tickets drawn in it (lower 16 bits), so that nothing has to clear
+// the words in front of a launch -- a launch of its own, 3 us of a 31 us layer: a word with
+// another tag, whatever wrote it, counts as no tickets.  Every workgroup looks at its word at its
+// start (peek) and, if the tag is not this launch's, swaps the word it saw for (tag, 0) before it
+// draws its own ticket (open); the swap fails if another workgroup was faster, and then the tag
+// is in place already.  The last ticket holder leaves (tag, 0).  peek returns what thread 0 saw.
+__device__ __forceinline__ uint64_t ticket_peek(const GemvParams& p, int strip, int G) {
+    uint64_t seen = p.epoch;
+    if (G > 1 && threadIdx.x == 0)
+        seen = __hip_atomic_load(&p.counters[strip], __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+    return seen;
+}
+__device__ __forceinline__ void ticket_open(const GemvParams& p, int strip, uint64_t seen) {
+    if ((seen ^ p.epoch) >> 16)
+        __hip_atomic_compare_exchange_strong(&p.counters[strip], &seen, p.epoch, __ATOMIC_RELAXED, __ATOMIC_RELAXED,
+                                             __HIP_MEMORY_SCOPE_AGENT);
+}
+
 // Combine the lanes' sums in a fixed order and write the strip's outputs: lane groups of one
 // wavefront (xor butterfly), wavefronts through `red` in index order, and -- with G > 1
 // workgroups per strip -- the workgroups through p.partial, added in workgroup order by the
 // one that draws the last ticket of p.counters[strip]; then the epilogue.
-// WRAP: the ticket counter returns to 0 with the last ticket (it must be 0 before the first
-// launch only); otherwise it counts up and the caller resets it between launches.
 // Returns after the outputs are written; `red` and `s_last` are LDS of the workgroup.
-template <typename WT, int LPR, int WAVES, int UNROLL, int NSEG, bool WRAP>
+template <typename WT, int LPR, int WAVES, int UNROLL, int NSEG>
 __device__ __forceinline__ void finish(const GemvParams& p, float (&acc)[NSEG][Elem<WT>::kPerLoad],
                                        int strip, int g, int G,
                                        float (&red)[WAVES][NSEG][LPR * Elem<WT>::kPerLoad], int& s_last) {
@@ -363,13 +380,10 @@ __device__ __forceinline__ void finish(const GemvParams& p, float (&acc)[NSEG][E
         asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
         __syncthreads();
         if (tid == 0) {
-            uint32_t prev;
-            if constexpr (WRAP) {
-                prev = atomicInc(&p.counters[strip], (uint32_t)(G - 1));
-            } else {
-                prev = __hip_atomic_fetch_add(&p.counters[strip], 1u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-            }
-            s_last = (prev == (uint32_t)(G - 1));
+            const uint64_t prev = __hip_atomic_fetch_add(&p.counters[strip], 1ull, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+            s_last = prev == p.epoch + (uint64_t)(G - 1);
+            // (every ticket is drawn: back to none for a replay of this launch from a graph)
+            if (s_last) __hip_atomic_store(&p.counters[strip], p.epoch, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
         }
         __syncthreads();
         if (!s_last) return;

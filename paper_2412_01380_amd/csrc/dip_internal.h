@@ -54,9 +54,6 @@ struct SelectParams {
     uint32_t* c_meta;
     int capacity;
     int policy;
-    // counters the following GEMV launch expects to be zero
-    uint32_t* zero_ptr;
-    int zero_n;
     // words of the columns this update evicted / inserted (nullable; only with a cache update)
     uint32_t* evicted_out;
     uint32_t* inserted_out;
@@ -112,7 +109,6 @@ struct CacheInitParams {
     int n;
 };
 hipError_t launch_cache_init(const CacheInitParams& p, hipStream_t stream);
-hipError_t launch_zero_u32(uint32_t* p, int n, hipStream_t stream);
 
 // ---- gathered GEMV -----------------------------------------------------------------------
 struct GemvShape {
@@ -137,7 +133,8 @@ struct GemvParams {
     int rows_per_split;       // ceil(k / ksplit), filled in by launch_gemv
     float* out;               // n_out floats (nseg == 2: the GLU output, n_out = d_ff)
     float* partial;           // [ksplit][nseg][n_out] when ksplit > 1
-    uint32_t* counters;       // [strips], zero on entry, when ksplit > 1
+    uint64_t* counters;       // [strips] when ksplit > 1, whatever they hold (see finish())
+    uint64_t epoch;           // this launch's tag in them, filled in by the launcher
     int act;                  // nseg == 1 only: 0 writes the sums, 1 writes SiLU of the sums
     const void* w_alt;        // second matrix for list entries r < 0 (stored row ~r), same dtype and
     int n_alt;                // row stride, n_alt rows; null / 0 when there is none
@@ -163,9 +160,14 @@ struct RowdotParams {
 };
 hipError_t launch_rowdot(const RowdotParams& p, hipStream_t stream, int prof_kind);
 
+uint64_t next_epoch();        // a tag for the ticket counters that no other launch has
 GemvShape choose_gemv_shape(int dtype, int n_out, int nseg, int k);
 int gemv_strips(const GemvShape& s, int dtype, int n_out);
 hipError_t launch_gemv(const GemvParams& p, const GemvShape& s, hipStream_t stream, int prof_kind);
+// nseg == 1 with p.idx a list of any alignment and x[idx[t]] the multipliers (p.val is ignored), in one
+// launch, for the shapes gather_in_gemv() names
+bool gather_in_gemv(const GemvShape& s, int k);
+hipError_t launch_gemv_gather(const GemvParams& p, const float* x, const GemvShape& s, hipStream_t stream, int prof_kind);
 // val[t] = x[idx[t]] (0 for an index outside [0, n)) and idx_copy[t] = idx[t], for t < k
 hipError_t launch_gather(const float* x, const int32_t* idx, int k, int n, float* val, int32_t* idx_copy,
                          hipStream_t stream);

@@ -90,8 +90,6 @@ __device__ __forceinline__ void select_body(SelectParams& p, SelShared& sh) {
     const int nwords = (p.n + 31) >> 5;
     int phase = 0;
 
-    for (int i = tid; i < p.zero_n; i += kSelThreads) p.zero_ptr[i] = 0u;
-
     // Features past n hold value 0 and key 0.  They sit at the highest indices, so the
     // lowest-index tie rule never picks them while k <= n, and they need no masking.
     float v[ITEMS];
@@ -423,7 +421,7 @@ __global__ __launch_bounds__(kSelThreads) void update_batch_kernel(UpdateWork wo
     p.mask_in = u.mask; p.scores_only = 0; p.s_out = nullptr; p.mask_out = nullptr;
     p.idx_out = nullptr; p.val_out = nullptr;
     p.c_bits = u.bits; p.c_stamp = u.stamp; p.c_meta = u.meta; p.capacity = u.capacity; p.policy = u.policy;
-    p.zero_ptr = nullptr; p.zero_n = 0; p.evicted_out = nullptr; p.inserted_out = nullptr;
+    p.evicted_out = nullptr; p.inserted_out = nullptr;
     select_body<ITEMS>(p, sh);
 }
 
@@ -450,11 +448,6 @@ __global__ void cache_init_kernel(CacheInitParams p) {
             p.meta[threadIdx.x] = val;
         }
     }
-}
-
-__global__ void zero_u32_kernel(uint32_t* p, int n) {
-    const int i = blockIdx.x * blockDim.x + threadIdx.x;
-    if (i < n) p[i] = 0u;
 }
 
 template <int ITEMS>
@@ -516,12 +509,6 @@ hipError_t launch_select(const SelectParams& p, hipStream_t stream, int prof_kin
 
 hipError_t launch_cache_init(const CacheInitParams& p, hipStream_t stream) {
     hipLaunchKernelGGL(cache_init_kernel, dim3(16), dim3(256), 0, stream, p);
-    return hipGetLastError();
-}
-
-hipError_t launch_zero_u32(uint32_t* p, int n, hipStream_t stream) {
-    if (n <= 0) return hipSuccess;
-    hipLaunchKernelGGL(zero_u32_kernel, dim3((n + 255) / 256), dim3(256), 0, stream, p, n);
     return hipGetLastError();
 }
 

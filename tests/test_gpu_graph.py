@@ -101,3 +101,51 @@ def test_batched_forward_replays_from_a_graph(D):
         for a, b in ((ce_in[0], cg_in[0]), (ce_mid[0], cg_mid[0])):
             assert np.array_equal(host_u32(a.bits), host_u32(b.bits)), (t, "residency")
             assert np.array_equal(host_u32(a.stamp), host_u32(b.stamp)), (t, "stamps")
+
+
+@pytest.mark.parametrize("call", ["forward", "gate", "gemv"])
+def test_split_products_expect_nothing_of_their_workspace(D, call):
+    """The workgroups of a split product count their arrivals in the workspace without anything
+    clearing it first: whatever the words hold -- zeros, ones, noise, what the previous call or
+    another call left -- every call gives the same bits, issued directly or replayed from a graph
+    whose workspace is overwritten between the replays."""
+    d, f, k_in, k_mid = 1024, 3072, 500, 1500
+    w = layer_weights(d, f, seed=23, layer=0, dtype="bf16")
+    up_gate, down = make_weight(D, w["ug"]), make_weight(D, w["d"])
+    x = dev_f32(ar1_laplace_stream(1, d, seed=9)[0])
+    if call == "forward":
+        mlp = D.Mlp(up_gate, down)
+        y = torch.empty(d, dtype=torch.float32, device="cuda")
+        nbytes = D.dip_swiglu_mlp_forward_workspace_bytes(mlp, k_in, k_mid)
+        run = lambda out, ws: D.dip_swiglu_mlp_forward(mlp, x, k_in, k_mid, None, None, 0.2, out, None, ws)
+    elif call == "gate":
+        rows = np.ascontiguousarray(w["ug"][:, :f].T), np.ascontiguousarray(w["ug"][:, f:])
+        split = D.MlpSplit(make_weight(D, rows[1]), make_weight(D, rows[0]), down)
+        y = torch.empty(d, dtype=torch.float32, device="cuda")
+        nbytes = D.dip_partial_pruning_forward_workspace_bytes(split, k_mid)
+        run = lambda out, ws: D.dip_partial_pruning_forward(split, D.DIP_GATE_PRUNING, x, k_mid, out, None, ws)
+    else:
+        idx = torch.arange(0, d, 2, dtype=torch.int32, device="cuda")
+        y = torch.empty(2 * f, dtype=torch.float32, device="cuda")
+        nbytes = D.dip_gathered_gemv_workspace_bytes(up_gate, d // 2)
+        run = lambda out, ws: D.dip_gathered_gemv(up_gate, x, idx, d // 2, out, ws)
+    ws = workspace(nbytes)
+    run(y, ws)
+    want = _bits(y).copy()
+    g = torch.Generator(device="cuda").manual_seed(1)
+    fills = [lambda: ws.zero_(), lambda: ws.fill_(0xFF), lambda: ws.random_(0, 256, generator=g), lambda: None]
+    for i, fill in enumerate(2 * fills):
+        fill()
+        run(y.fill_(0), ws)
+        assert np.array_equal(_bits(y), want), i
+    graph = torch.cuda.CUDAGraph()
+    with torch.cuda.graph(graph):
+        run(y, ws)
+    for i, fill in enumerate(2 * fills + fills[::-1]):
+        fill()
+        if i % 3 == 1:
+            run(y, ws)          # another launch's tags in the same words
+        y.fill_(0)
+        graph.replay()
+        torch.cuda.synchronize()
+        assert np.array_equal(_bits(y), want), (i, "replay")

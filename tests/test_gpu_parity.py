@@ -293,6 +293,44 @@ def test_gathered_gemv_launch_shapes(D, fmt, lpr, waves, ksplit, unroll):
         D.dip_tune_gemv(0, 0, 0, 0)
 
 
+@pytest.mark.parametrize("fmt", ["f32", "bf16"])
+def test_gathered_gemv_list_forms(D, fmt):
+    """The list goes through LDS up to 2048 rows of a share and through the workspace above that; it
+    may start at any element, name rows outside the matrix, and share memory with the output."""
+    n_in, n_out = 2100, 2104
+    w = layer_weights(n_in, n_out // 2, seed=10, dtype=fmt)["ug"]
+    W = D.Weight(dev_weight(w))
+    x = studentt_tokens(1, n_in, seed=3)[0]
+    try:
+        for tune in ((0, 0, 0, 0), (16, 8, 1, 4), (16, 8, 3, 4)):
+            D.dip_tune_gemv(*tune)
+            for k in (1, 7, 8, 9, 2047, 2048, 2049, 2100):
+                _, idx = O.topk(np.abs(x), k)
+                ref = O.gathered_gemv(w, x, idx)
+                ws = workspace(D.dip_gathered_gemv_workspace_bytes(W, k))
+                ws.fill_(0xFF)
+                y = torch.empty(n_out, dtype=torch.float32, device="cuda")
+                at = torch.full((k + 3,), -5, dtype=torch.int32, device="cuda")
+                at[1:k + 1] = torch.from_numpy(idx.astype(np.int32)).cuda()
+                D.dip_gathered_gemv(W, dev_f32(x), at[1:k + 1], k, y, ws)
+                assert_product_close(y.cpu().numpy(), ref, fmt, k)
+                both = torch.zeros(n_out, dtype=torch.float32, device="cuda")     # x and y in one buffer
+                both[:n_in] = dev_f32(x)
+                D.dip_gathered_gemv(W, both[:n_in], at[1:k + 1], k, both, ws)
+                assert_product_close(both.cpu().numpy(), ref, fmt, k)
+        k = 40
+        idx = np.arange(0, 2 * k, 2).astype(np.int32)
+        out = idx.copy()
+        out[5], out[30] = n_in, -3                        # outside: they contribute nothing
+        ref = O.gathered_gemv(w, x, np.delete(idx, [5, 30]))
+        ws = workspace(D.dip_gathered_gemv_workspace_bytes(W, k))
+        y = torch.empty(n_out, dtype=torch.float32, device="cuda")
+        D.dip_gathered_gemv(W, dev_f32(x), torch.from_numpy(out).cuda(), k, y, ws)
+        assert_product_close(y.cpu().numpy(), ref, fmt, k)
+    finally:
+        D.dip_tune_gemv(0, 0, 0, 0)
+
+
 # ------------------------------------------------------------------ fused forward, stage replay
 def _stage_replay(D, w, x, k_in, k_mid, tol, cache_pair=None, oracle_caches=None, gamma=0.2):
     """One token through the GPU forward; every stage checked against the oracle applied to
