@@ -296,8 +296,8 @@ StackPlan plan_stack(const dip_mlp* mlp, const int32_t* k_in, const int32_t* k_m
     // (a workspace sized for a stack serves every part of it: fewer layers get more shares each)
     size_t part_words = 0;
     for (int m = layers < kMinStackLayers ? layers : kMinStackLayers; m <= layers; ++m) {
-        pl.g1 = stack_shares(mlp->w_ug.dtype, 2 * pl.f, pl.k1max, m);
-        pl.g2 = stack_shares(mlp->w_d.dtype, pl.d, pl.k2max, m);
+        pl.g1 = stack_shares(mlp->w_ug.dtype, 2 * pl.f, pl.k1max, m, 1);
+        pl.g2 = stack_shares(mlp->w_d.dtype, pl.d, pl.k2max, m, 1);
         pl.part = align_up(std::max((size_t)pl.g1 * 2 * pl.f, (size_t)pl.g2 * pl.d), 64);
         part_words = std::max(part_words, pl.part * m);
     }
@@ -376,6 +376,7 @@ int32_t forward_stack_group(const dip_mlp* mlps, int layers, const float* x, int
         std::memset(&gp, 0, sizeof(gp));
         gp.row_stride = w0.row_stride_bytes; gp.scale_stride = w0.n_out / 128; gp.n_in = w0.n_in; gp.n_out = w0.n_out;
         gp.idx = idx; gp.val = val; gp.list_layer_stride = sp.list_layer_stride;
+        gp.rows = 1;
         gp.out = part; gp.out_layer_stride = pl.part;
         for (int l = 0; l < layers; ++l) {
             const dip_weight& w = pt == 0 ? mlps[l].w_ug : mlps[l].w_d;
@@ -716,7 +717,8 @@ namespace {
 // (one layer: a phase each).  Sizes are per layer, in words.
 struct BatchedPlan {
     int d, f, wd, wf, k1max, k2max, g1, g2;
-    bool mc1, mc2;             // product on the matrix cores
+    bool mc1, mc2;             // product on the matrix cores ...
+    bool st1, st2;             // ... or by the kernel of the stacks (otherwise by bgemv_kernel)
     size_t masks1, masks2, list1, list2, h, part;
     size_t off_rmax, off_cnt, off_m1, off_idx1, off_val1, off_m2, off_idx2, off_val2, off_h, off_part;
     size_t total;
@@ -736,11 +738,23 @@ BatchedPlan plan_batched(const dip_mlp* mlp, int B, const int32_t* k_in, const i
     pl.mc2 = batched_on_matrix_cores(mlp->w_d.dtype, B, mlp->w_d.n_in, mlp->w_d.row_stride_bytes);
     // (a workspace sized for a stack serves every part of it: fewer layers get more shares each)
     size_t part_words = 0;
+    // (... and smaller k in a part of it may take it to the other kernel)
     for (int m = 1; m <= layers; ++m) {
-        pl.g1 = batched_shares(mlp->w_ug.dtype, 2 * pl.f, pl.k1max, pl.mc1, m);
-        pl.g2 = batched_shares(mlp->w_d.dtype, pl.d, pl.k2max, pl.mc2, m);
-        pl.part = align_up(std::max((size_t)pl.g1 * B * 2 * pl.f, (size_t)pl.g2 * B * pl.d), 64);
-        part_words = std::max(part_words, pl.part * m);
+        int g[2][2];
+        const dip_weight* w[2] = {&mlp->w_ug, &mlp->w_d};
+        for (int pt = 0; pt < 2; ++pt) {
+            const int kmax = pt == 0 ? pl.k1max : pl.k2max;
+            const bool mc = pt == 0 ? pl.mc1 : pl.mc2;
+            g[pt][0] = batched_shares(w[pt]->dtype, w[pt]->n_out, kmax, mc, m);
+            g[pt][1] = mc || m < 4 ? 0 : stack_shares(w[pt]->dtype, w[pt]->n_out, kmax, m, B);
+        }
+        pl.st1 = !pl.mc1 && stack_pays(mlp->w_ug.dtype, 2 * pl.f, pl.k1max, m, B);
+        pl.st2 = !pl.mc2 && stack_pays(mlp->w_d.dtype, pl.d, pl.k2max, m, B);
+        pl.g1 = g[0][pl.st1];
+        pl.g2 = g[1][pl.st2];
+        auto words = [&](int g1, int g2) { return align_up(std::max((size_t)g1 * B * 2 * pl.f, (size_t)g2 * B * pl.d), 64); };
+        pl.part = words(pl.g1, pl.g2);
+        part_words = std::max(part_words, words(std::max(g[0][0], g[0][1]), std::max(g[1][0], g[1][1])) * m);
     }
     pl.masks1 = align_up((size_t)B * pl.wd, 64);
     pl.masks2 = align_up((size_t)B * pl.wf, 64);
@@ -796,7 +810,7 @@ namespace {
 // The union masks go to `uwords` (two per layer) and the cache updates with them are left to the
 // caller (one launch at the end of the call).  The stage outputs (nullable) take layers == 1.
 // Measured per layer-step over 40 layers of the Phi-3-Medium shape with int4 weights: layer by
-// layer 62.8 us at two rows and 83.8 us at eight, in phases 17.6 and 36.2 us.
+// layer 62.8 us at two rows and 83.8 us at eight, in phases 14.2 and 21.4 us.
 int32_t batched_group(const dip_mlp* mlps, int layers, const float* X, int64_t x_stride, int batch, const int32_t* k_in,
                       const int32_t* k_mid, int k_stride, const dip_cache* caches_in, const dip_cache* caches_mid,
                       float gamma, float* Y, int64_t y_stride, uint32_t* mask_in_out, float* h_out,
@@ -812,16 +826,16 @@ int32_t batched_group(const dip_mlp* mlps, int layers, const float* X, int64_t x
 
     struct Point {
         const float* v; int64_t v_stride; int n, kmax, words; const int32_t* k; const dip_cache* caches; uint32_t* masks;
-        size_t masks_stride, list; int32_t* uidx; float* uval; int shares; bool mc; int select_kind, gemv_kind;
+        size_t masks_stride, list; int32_t* uidx; float* uval; int shares; bool mc, st; int select_kind, gemv_kind;
     };
     const Point pts[2] = {
         {X, x_stride, pl.d, pl.k1max, pl.wd, k_in, caches_in,
          mask_in_out ? mask_in_out : reinterpret_cast<uint32_t*>(base + pl.off_m1), pl.masks1, pl.list1,
-         reinterpret_cast<int32_t*>(base + pl.off_idx1), reinterpret_cast<float*>(base + pl.off_val1), pl.g1, pl.mc1,
+         reinterpret_cast<int32_t*>(base + pl.off_idx1), reinterpret_cast<float*>(base + pl.off_val1), pl.g1, pl.mc1, pl.st1,
          DIP_KERNEL_SELECT_IN, DIP_KERNEL_GEMV_UPGATE},
         {H, (int64_t)pl.h, pl.f, pl.k2max, pl.wf, k_mid, caches_mid,
          mask_mid_out ? mask_mid_out : reinterpret_cast<uint32_t*>(base + pl.off_m2), pl.masks2, pl.list2,
-         reinterpret_cast<int32_t*>(base + pl.off_idx2), reinterpret_cast<float*>(base + pl.off_val2), pl.g2, pl.mc2,
+         reinterpret_cast<int32_t*>(base + pl.off_idx2), reinterpret_cast<float*>(base + pl.off_val2), pl.g2, pl.mc2, pl.st2,
          DIP_KERNEL_SELECT_MID, DIP_KERNEL_GEMV_DOWN}};
     for (int pt = 0; pt < 2; ++pt) {
         const Point& q = pts[pt];
@@ -850,20 +864,35 @@ int32_t batched_group(const dip_mlp* mlps, int layers, const float* X, int64_t x
             updates.push_back(update_piece(q.caches[l], uwords + (2 * l + pt) * kMaskWords));
         // gathered product for all rows, then the reduction with its epilogue
         const dip_weight& w0 = pt == 0 ? mlps[0].w_ug : mlps[0].w_d;
-        BatchedGemvParams gp;
-        std::memset(&gp, 0, sizeof(gp));
-        gp.row_stride = w0.row_stride_bytes; gp.scale_stride = w0.n_out / 128;
-        gp.dtype = w0.dtype; gp.n_in = w0.n_in; gp.n_out = w0.n_out;
-        gp.uidx = q.uidx; gp.uval = q.uval; gp.list_layer_stride = q.list; gp.k_dev = up.count_out; gp.k_max = q.kmax;
-        gp.batch = batch; gp.partial = part; gp.partial_layer_stride = pl.part; gp.rowmax = sp.rowmax_out;
-        for (int l = 0; l < layers; ++l) {
-            const dip_weight& w = pt == 0 ? mlps[l].w_ug : mlps[l].w_d;
-            gp.layer[l].w = w.data;
-            gp.layer[l].scales = static_cast<const uint16_t*>(w.scales);
+        if (q.st) {
+            StackProductParams gp;
+            std::memset(&gp, 0, sizeof(gp));
+            gp.row_stride = w0.row_stride_bytes; gp.scale_stride = w0.n_out / 128; gp.n_in = w0.n_in; gp.n_out = w0.n_out;
+            gp.idx = q.uidx; gp.val = q.uval; gp.list_layer_stride = q.list; gp.rows = batch;
+            gp.k_dev = up.count_out; gp.k_max = q.kmax; gp.out = part; gp.out_layer_stride = pl.part;
+            for (int l = 0; l < layers; ++l) {
+                const dip_weight& w = pt == 0 ? mlps[l].w_ug : mlps[l].w_d;
+                gp.layer[l].w = w.data;
+                gp.layer[l].scales = static_cast<const uint16_t*>(w.scales);
+            }
+            st = check_hip(launch_stack_product(gp, w0.dtype, q.shares, layers, hs, q.gemv_kind),
+                           "forward_batched: gathered product");
+        } else {
+            BatchedGemvParams gp;
+            std::memset(&gp, 0, sizeof(gp));
+            gp.row_stride = w0.row_stride_bytes; gp.scale_stride = w0.n_out / 128;
+            gp.dtype = w0.dtype; gp.n_in = w0.n_in; gp.n_out = w0.n_out;
+            gp.uidx = q.uidx; gp.uval = q.uval; gp.list_layer_stride = q.list; gp.k_dev = up.count_out; gp.k_max = q.kmax;
+            gp.batch = batch; gp.partial = part; gp.partial_layer_stride = pl.part; gp.rowmax = sp.rowmax_out;
+            for (int l = 0; l < layers; ++l) {
+                const dip_weight& w = pt == 0 ? mlps[l].w_ug : mlps[l].w_d;
+                gp.layer[l].w = w.data;
+                gp.layer[l].scales = static_cast<const uint16_t*>(w.scales);
+            }
+            st = check_hip(launch_batched_gemv(gp, q.shares, q.mc, layers, hs, q.gemv_kind),
+                           "forward_batched: gathered product");
         }
-        if ((st = check_hip(launch_batched_gemv(gp, q.shares, q.mc, layers, hs, q.gemv_kind),
-                            "forward_batched: gathered product")))
-            return st;
+        if (st) return st;
         BatchedReduceParams rp;
         std::memset(&rp, 0, sizeof(rp));
         rp.partial = part; rp.partial_layer_stride = pl.part; rp.shares = q.shares; rp.batch = batch; rp.n_out = w0.n_out;

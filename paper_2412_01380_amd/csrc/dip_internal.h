@@ -210,10 +210,13 @@ struct StackProductParams {
     int scale_stride;
     int n_in;
     int n_out;                // elements per stored row (both halves of a bundled row)
-    const int32_t* idx;       // lists of layer l: idx + l * list_layer_stride, ascending
-    const float* val;
+    const int32_t* idx;       // lists of layer l: idx + l * list_layer_stride, ascending; the `rows`
+    const float* val;         // multipliers of an entry side by side: val + l * list_layer_stride * rows
     int64_t list_layer_stride;
-    float* out;               // sums of share g of layer l: out + l * out_layer_stride + g * n_out
+    int rows;                 // batch rows, 1 .. 8
+    int k_max;                // capacity of the lists
+    const uint32_t* k_dev;    // their lengths in device memory, one word per layer, or null: layer[].k
+    float* out;               // sums of share g of layer l: out + l * out_layer_stride + (g * rows + row) * n_out
     int64_t out_layer_stride;
     struct Layer {
         const void* w;
@@ -222,7 +225,9 @@ struct StackProductParams {
         int pad;
     } layer[kStackLayers];
 };
-int stack_shares(int dtype, int n_out, int k_max, int layers);
+int stack_shares(int dtype, int n_out, int k_max, int layers, int rows);
+// whether a small batch's product over these layers has enough workgroups for this kernel
+bool stack_pays(int dtype, int n_out, int k_max, int layers, int rows);
 hipError_t launch_stack_product(const StackProductParams& p, int dtype, int shares, int layers, hipStream_t stream,
                                 int prof_kind);
 

@@ -16,6 +16,9 @@
 // Up and gate halves of a bundled row are just more columns here; the reduction launch behind
 // the product adds the shares and applies SwiGLU.
 //
+// A small batch reads the union of its rows' lists with one multiplier per batch row, which stay
+// scalar; the row of weights is widened once for all of them.
+//
 // int4 rows are a quarter of the bytes and bound by vector instructions: see Q4.
 #include "dip_internal.h"
 
@@ -31,23 +34,27 @@ struct F32 {
     typedef u32x4 raw_t;
     static constexpr int kElems = 4, kBits = 32;
     static constexpr bool kScaled = false;
-    __device__ static __forceinline__ void fma(const raw_t& q, float m, float (&acc)[4]) {
-        acc[0] = fmaf(__uint_as_float(q.x), m, acc[0]);
-        acc[1] = fmaf(__uint_as_float(q.y), m, acc[1]);
-        acc[2] = fmaf(__uint_as_float(q.z), m, acc[2]);
-        acc[3] = fmaf(__uint_as_float(q.w), m, acc[3]);
+    template <int B>
+    __device__ static __forceinline__ void fma(const raw_t& q, const float (&m)[B], float (&acc)[B][4]) {
+#pragma unroll
+        for (int i = 0; i < 4; ++i)
+#pragma unroll
+            for (int b = 0; b < B; ++b) acc[b][i] = fmaf(__uint_as_float(q[i]), m[b], acc[b][i]);
     }
 };
 struct Bf16 {  // the upper half of an fp32 pattern
     typedef u32x4 raw_t;
     static constexpr int kElems = 8, kBits = 16;
     static constexpr bool kScaled = false;
-    __device__ static __forceinline__ void fma(const raw_t& q, float m, float (&acc)[8]) {
+    template <int B>
+    __device__ static __forceinline__ void fma(const raw_t& q, const float (&m)[B], float (&acc)[B][8]) {
 #pragma unroll
-        for (int i = 0; i < 4; ++i) {
-            acc[2 * i] = fmaf(__uint_as_float(q[i] << 16), m, acc[2 * i]);
-            acc[2 * i + 1] = fmaf(__uint_as_float(q[i] & 0xffff0000u), m, acc[2 * i + 1]);
-        }
+        for (int i = 0; i < 4; ++i)
+#pragma unroll
+            for (int b = 0; b < B; ++b) {
+                acc[b][2 * i] = fmaf(__uint_as_float(q[i] << 16), m[b], acc[b][2 * i]);
+                acc[b][2 * i + 1] = fmaf(__uint_as_float(q[i] & 0xffff0000u), m[b], acc[b][2 * i + 1]);
+            }
     }
 };
 struct Q4 {
@@ -70,36 +77,46 @@ struct Q4 {
         return (float)__builtin_bit_cast(_Float16, b);
     }
     // m24 = multiplier * 2^12 for codes in bits 0-3 of a half, m20 = multiplier * 2^8 for bits 4-7
-    __device__ static __forceinline__ void fma(const raw_t& q, float m24, float m20, float (&acc)[16]) {
+    template <int B>
+    __device__ static __forceinline__ void fma(const raw_t& q, const float (&m24)[B], const float (&m20)[B],
+                                               float (&acc)[B][16]) {
 #pragma unroll
         for (int i = 0; i < 2; ++i) {
             const uint32_t o = q[i] ^ 0x88888888u, o8 = o >> 8;
             const uint32_t c04 = o & 0x000f000fu, c15 = o & 0x00f000f0u;
             const uint32_t c26 = o8 & 0x000f000fu, c37 = o8 & 0x00f000f0u;
-            float* a = acc + 8 * i;
-            a[0] = fmaf(lo(c04), m24, a[0]);
-            a[4] = fmaf(hi(c04), m24, a[4]);
-            a[1] = fmaf(lo(c15), m20, a[1]);
-            a[5] = fmaf(hi(c15), m20, a[5]);
-            a[2] = fmaf(lo(c26), m24, a[2]);
-            a[6] = fmaf(hi(c26), m24, a[6]);
-            a[3] = fmaf(lo(c37), m20, a[3]);
-            a[7] = fmaf(hi(c37), m20, a[7]);
+#pragma unroll
+            for (int b = 0; b < B; ++b) {
+                float* a = acc[b] + 8 * i;
+                a[0] = fmaf(lo(c04), m24[b], a[0]);
+                a[4] = fmaf(hi(c04), m24[b], a[4]);
+                a[1] = fmaf(lo(c15), m20[b], a[1]);
+                a[5] = fmaf(hi(c15), m20[b], a[5]);
+                a[2] = fmaf(lo(c26), m24[b], a[2]);
+                a[6] = fmaf(hi(c26), m24[b], a[6]);
+                a[3] = fmaf(lo(c37), m20[b], a[3]);
+                a[7] = fmaf(hi(c37), m20[b], a[7]);
+            }
         }
     }
 };
 
-constexpr int kWaves = 8;     // wavefronts per workgroup
-constexpr int kBlock = 8;     // selected rows in flight per wavefront and register set
+// Wavefronts per workgroup and, for each, rows in flight per register set.  With one batch row
+// eight of both; with more, whose sums and multipliers fill registers, four of both, so that a
+// register or two more do not cost eight wavefronts of a compute unit (two rows of int4, 40
+// layers of the Phi-3-Medium shape: 698 us with eight of both, 568 with four).
+template <int B>
+struct Shape { static constexpr int kWaves = B == 1 ? 8 : 4, kBlock = B == 1 ? 8 : 4; };
 
-template <typename E>
-__global__ __launch_bounds__(kWaves * 64) void stack_product_kernel(StackProductParams p) {
+template <typename E, int B>
+__global__ __launch_bounds__(Shape<B>::kWaves * 64) void stack_product_kernel(StackProductParams p) {
     constexpr int EPL = E::kElems, SC = 64 * EPL;
+    constexpr int kWaves = Shape<B>::kWaves, kBlock = Shape<B>::kBlock;
     __shared__ float red[kWaves][SC];
     const int tid = threadIdx.x, lane = tid & 63;
     const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
     const int strip = blockIdx.x, g = blockIdx.y, G = gridDim.y, layer = blockIdx.z;
-    const int k = p.layer[layer].k;
+    const int k = p.k_dev ? min((int)p.k_dev[layer], p.k_max) : p.layer[layer].k;
     const int share = ((k + G - 1) / G + kBlock - 1) / kBlock * kBlock;
     const int kb = min(k, g * share), ke = min(k, kb + share);
 
@@ -111,19 +128,24 @@ __global__ __launch_bounds__(kWaves * 64) void stack_product_kernel(StackProduct
     const uint32_t sgroup = (uint32_t)col >> 7;
     // uniform addresses in the constant address space: scalar loads
     const DIP_CONSTANT int32_t* idx = (const DIP_CONSTANT int32_t*)(uintptr_t)(p.idx + layer * p.list_layer_stride);
-    const DIP_CONSTANT float* val = (const DIP_CONSTANT float*)(uintptr_t)(p.val + layer * p.list_layer_stride);
+    const DIP_CONSTANT float* val = (const DIP_CONSTANT float*)(uintptr_t)(p.val + layer * p.list_layer_stride * B);
 
-    float acc[EPL], msum = 0.f;
+    float acc[B][EPL], msum[B];
 #pragma unroll
-    for (int e = 0; e < EPL; ++e) acc[e] = 0.f;
+    for (int b = 0; b < B; ++b) {
+        msum[b] = 0.f;
+#pragma unroll
+        for (int e = 0; e < EPL; ++e) acc[b][e] = 0.f;
+    }
 
-    struct Pairs { int r[kBlock]; float m[kBlock]; };
+    struct Pairs { int r[kBlock]; float m[kBlock][B]; };
     struct Rows { typename E::raw_t q[kBlock]; uint16_t sc[kBlock]; };
     auto fetch = [&](int t, Pairs& b) {
 #pragma unroll
         for (int u = 0; u < kBlock; ++u) {
             b.r[u] = idx[t + u];
-            b.m[u] = val[t + u];
+#pragma unroll
+            for (int i = 0; i < B; ++i) b.m[u][i] = val[(t + u) * B + i];
         }
     };
     auto request = [&](const Pairs& b, Rows& x) {
@@ -136,17 +158,25 @@ __global__ __launch_bounds__(kWaves * 64) void stack_product_kernel(StackProduct
             if constexpr (E::kScaled) x.sc[u] = (scales + (size_t)r * (size_t)p.scale_stride)[sgroup];
         }
     };
+    auto multiply_row = [&](const typename E::raw_t& q, uint16_t sc, const float (&m)[B]) {
+        if constexpr (E::kScaled) {
+            const float scale = (float)__builtin_bit_cast(_Float16, sc);
+            float m24[B], m20[B];
+#pragma unroll
+            for (int i = 0; i < B; ++i) {
+                const float mult = m[i] * scale;
+                msum[i] += mult;
+                m24[i] = mult * E::kUp;
+                m20[i] = mult * (E::kUp / 16.0f);
+            }
+            E::template fma<B>(q, m24, m20, acc);
+        } else {
+            E::template fma<B>(q, m, acc);
+        }
+    };
     auto multiply = [&](const Pairs& b, const Rows& x) {
 #pragma unroll
-        for (int u = 0; u < kBlock; ++u) {
-            if constexpr (E::kScaled) {
-                const float mult = b.m[u] * (float)__builtin_bit_cast(_Float16, x.sc[u]);
-                msum += mult;
-                E::fma(x.q[u], mult * E::kUp, mult * (E::kUp / 16.0f), acc);
-            } else {
-                E::fma(x.q[u], b.m[u], acc);
-            }
-        }
+        for (int u = 0; u < kBlock; ++u) multiply_row(x.q[u], E::kScaled ? x.sc[u] : (uint16_t)0, b.m[u]);
     };
 
     // full blocks t = kb + (wave + i * kWaves) * kBlock
@@ -178,62 +208,93 @@ __global__ __launch_bounds__(kWaves * 64) void stack_product_kernel(StackProduct
     const int rest = kb + n_blocks * kBlock + wave;
     if (rest < ke) {
         const int r0 = idx[rest];
-        const float m = val[rest];
+        float m[B];
+#pragma unroll
+        for (int i = 0; i < B; ++i) m[i] = val[rest * B + i];
         const uint32_t r = (uint32_t)r0 < (uint32_t)p.n_in ? (uint32_t)r0 : 0u;
         const typename E::raw_t q = __builtin_nontemporal_load(
             reinterpret_cast<const typename E::raw_t*>(w + (size_t)r * (size_t)p.row_stride + voff));
-        if constexpr (E::kScaled) {
-            const float mult = m * (float)__builtin_bit_cast(_Float16, (scales + (size_t)r * (size_t)p.scale_stride)[sgroup]);
-            msum += mult;
-            E::fma(q, mult * E::kUp, mult * (E::kUp / 16.0f), acc);
-        } else {
-            E::fma(q, m, acc);
-        }
+        uint16_t sc = 0;
+        if constexpr (E::kScaled) sc = (scales + (size_t)r * (size_t)p.scale_stride)[sgroup];
+        multiply_row(q, sc, m);
     }
     static_assert(kBlock <= kWaves, "one leftover row per wavefront");
-    if constexpr (E::kScaled) {
-#pragma unroll
-        for (int e = 0; e < EPL; ++e) acc[e] = fmaf(-8.0f, msum, acc[e] * E::kUp);
-    }
-
     // wavefronts through LDS, added in order
 #pragma unroll
-    for (int e = 0; e < EPL; e += 4)
-        *reinterpret_cast<float4*>(&red[wave][lane * EPL + e]) = make_float4(acc[e], acc[e + 1], acc[e + 2], acc[e + 3]);
-    __syncthreads();
-    float* out = p.out + layer * p.out_layer_stride + (int64_t)g * p.n_out;
+    for (int b = 0; b < B; ++b) {
+        if constexpr (E::kScaled) {
 #pragma unroll
-    for (int c0 = 0; c0 < SC; c0 += kWaves * 64) {
-        const int c = c0 + tid;
-        const int gcol = strip * SC + c;
-        if (c < SC && gcol < p.n_out) {
-            float s = 0.f;
+            for (int e = 0; e < EPL; ++e) acc[b][e] = fmaf(-8.0f, msum[b], acc[b][e] * E::kUp);
+        }
+        if (b > 0) __syncthreads();
 #pragma unroll
-            for (int i = 0; i < kWaves; ++i) s += red[i][c];
-            out[gcol] = s;
+        for (int e = 0; e < EPL; e += 4)
+            *reinterpret_cast<float4*>(&red[wave][lane * EPL + e]) =
+                make_float4(acc[b][e], acc[b][e + 1], acc[b][e + 2], acc[b][e + 3]);
+        __syncthreads();
+        float* out = p.out + layer * p.out_layer_stride + ((int64_t)g * B + b) * p.n_out;
+#pragma unroll
+        for (int c0 = 0; c0 < SC; c0 += kWaves * 64) {
+            const int c = c0 + tid;
+            const int gcol = strip * SC + c;
+            if (c < SC && gcol < p.n_out) {
+                float s = 0.f;
+#pragma unroll
+                for (int i = 0; i < kWaves; ++i) s += red[i][c];
+                out[gcol] = s;
+            }
         }
     }
 }
 
+// (int4 batches of three and more run on the matrix cores)
+template <typename E>
+hipError_t launch_rows(const StackProductParams& p, dim3 grid, dim3 block, hipStream_t stream, int pk) {
+    if (p.rows == 1) return launch_timed(stack_product_kernel<E, 1>, grid, block, stream, pk, p);
+    if (p.rows == 2) return launch_timed(stack_product_kernel<E, 2>, grid, block, stream, pk, p);
+    if constexpr (!E::kScaled) switch (p.rows) {
+        case 3: return launch_timed(stack_product_kernel<E, 3>, grid, block, stream, pk, p);
+        case 4: return launch_timed(stack_product_kernel<E, 4>, grid, block, stream, pk, p);
+        case 5: return launch_timed(stack_product_kernel<E, 5>, grid, block, stream, pk, p);
+        case 6: return launch_timed(stack_product_kernel<E, 6>, grid, block, stream, pk, p);
+        case 7: return launch_timed(stack_product_kernel<E, 7>, grid, block, stream, pk, p);
+        case 8: return launch_timed(stack_product_kernel<E, 8>, grid, block, stream, pk, p);
+    }
+    return hipErrorInvalidValue;
+}
+
 }  // namespace
 
-int stack_shares(int dtype, int n_out, int k_max, int layers) {
+static int stack_strips(int dtype, int n_out) {
     const int sc = 64 * (dtype == DIP_F32 ? 4 : (dtype == DIP_BF16 ? 8 : 16));
-    const int strips = (n_out + sc - 1) / sc;
-    const int wgs = strips * layers;
-    int g = (k_max + 383) / 384;
-    while (wgs * g < 1024 && k_max / (g + 1) >= kWaves * kBlock) ++g;
+    return (n_out + sc - 1) / sc;
+}
+
+bool stack_pays(int dtype, int n_out, int k_max, int layers, int rows) {
+    // Four workgroups fit a compute unit: one round of them with 512 listed columns each.  Below
+    // that the narrower strips of bgemv_kernel fill the chip better (12 layers of 1024 x 3072 in
+    // bf16 at 6 rows: 75 against 89 us per step; 40 of 2048 x 7168 at 8 rows: 557 against 474).
+    if (dtype == DIP_INT4_G128 && rows > 2) return false;
+    return layers >= 4 && (int64_t)stack_strips(dtype, n_out) * layers * ((k_max + 511) / 512) >= 1024;
+}
+
+int stack_shares(int dtype, int n_out, int k_max, int layers, int rows) {
+    const int wgs = stack_strips(dtype, n_out) * layers;
+    // (the sums of a share are written and read once per batch row: longer shares for more rows)
+    const int kLong = rows == 1 ? 384 : 1536, target = rows == 1 ? 1024 : 2048, least = rows == 1 ? 64 : 256;
+    int g = (k_max + kLong - 1) / kLong;
+    while (wgs * g < target && k_max / (g + 1) >= least) ++g;
     return g < 1 ? 1 : g;
 }
 
 hipError_t launch_stack_product(const StackProductParams& p, int dtype, int shares, int layers, hipStream_t stream,
                                 int pk) {
     if (!p.idx || !p.val || !p.out || layers < 1 || layers > kStackLayers || shares < 1) return hipErrorInvalidValue;
-    const int sc = 64 * (dtype == DIP_F32 ? 4 : (dtype == DIP_BF16 ? 8 : 16));
-    const dim3 grid((p.n_out + sc - 1) / sc, shares, layers), block(kWaves * 64);
-    if (dtype == DIP_F32) return launch_timed(stack_product_kernel<F32>, grid, block, stream, pk, p);
-    if (dtype == DIP_BF16) return launch_timed(stack_product_kernel<Bf16>, grid, block, stream, pk, p);
-    if (dtype == DIP_INT4_G128) return launch_timed(stack_product_kernel<Q4>, grid, block, stream, pk, p);
+    const dim3 grid(stack_strips(dtype, p.n_out), shares, layers),
+        block(64 * (p.rows == 1 ? Shape<1>::kWaves : Shape<2>::kWaves));
+    if (dtype == DIP_F32) return launch_rows<F32>(p, grid, block, stream, pk);
+    if (dtype == DIP_BF16) return launch_rows<Bf16>(p, grid, block, stream, pk);
+    if (dtype == DIP_INT4_G128) return launch_rows<Q4>(p, grid, block, stream, pk);
     return hipErrorInvalidValue;
 }
 

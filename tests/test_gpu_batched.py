@@ -225,15 +225,17 @@ def test_batched_stack_in_phases_matches_per_layer_calls(D, fmt, B):
                 assert torch.equal(a.bits, b.bits) and torch.equal(a.stamp, b.stamp) and torch.equal(a.meta, b.meta), (t, l)
 
 
-@pytest.mark.parametrize("B", [3, 8])
-def test_batched_int4_stack_wide_workgroups(D, B):
-    """Many layers of one shape: the matrix-core product runs with its wavefronts side by side
-    (strips of 1024 stored columns, here ragged ones: 66 and 9 groups), the list staged in chunks of
-    512, with union sizes from one column to all at the edges of sets, chunks and shares.  The
-    one-layer calls split the same terms over other workgroups: only the order of the fp32 sums
-    differs (a few 1e-7)."""
+@pytest.mark.parametrize("fmt,B", [("int4", 3), ("int4", 8), ("int4", 1), ("int4", 2), ("bf16", 1), ("bf16", 3),
+                                   ("bf16", 8), ("f32", 2), ("f32", 5)])
+def test_batched_stack_of_many_layers(D, fmt, B):
+    """Many layers of one shape, enough for the products that take whole strips of a row per
+    workgroup: on the matrix cores with the wavefronts side by side (strips of 1024 stored columns,
+    here ragged ones: 66 and 9 groups, the list staged in chunks of 512), otherwise by the kernel of
+    the stacks (strips of 256 to 1024).  Union sizes from one column to all, at the edges of sets,
+    blocks, chunks and shares.  The one-layer calls split the same terms over other workgroups: only
+    the order of the fp32 sums differs (a few 1e-7)."""
     d, f, L = 1152, 4224, 64
-    w = layer_weights(d, f, seed=64, layer=0, dtype="int4")
+    w = layer_weights(d, f, seed=64, layer=0, dtype=fmt)
     mlp = D.Mlp(make_weight(D, w["ug"]), make_weight(D, w["d"]))
     k_in = [d] * L
     k_in[:8] = [1, 31, 32, 33, 170, 191, 200, 400]
