@@ -95,7 +95,6 @@ int32_t validate_gamma(float gamma) {
 // [ mask words of every layer: point 1, point 2 ]  kept until the cache updates at the end of the call
 // [ scratch of one layer, shared by all layers   ]  index lists, h~, partial sums, ticket counters
 constexpr size_t kMaskBytes = sizeof(uint32_t) * (DIP_MAX_N / 32);
-constexpr int kMaxCounters = 1024;   // strips of a product, at the narrowest strip width
 
 struct ForwardPlan {
     int d, f;
@@ -120,7 +119,7 @@ ForwardPlan plan_forward(const dip_mlp* mlp, int k_in, int k_mid) {
     size_t o = 0;
     auto take = [&](size_t bytes) { size_t at = o; o = align_up(o + bytes, 256); return at; };
     // ticket counters, the same for both products (a launch tells its own tickets by their tag)
-    pl.off_cnt = take(sizeof(uint64_t) * kMaxCounters);
+    pl.off_cnt = take(sizeof(uint64_t) * kTicketWords);
     pl.off_idx1 = take(sizeof(int32_t) * k_in);
     pl.off_val1 = take(sizeof(float) * k_in);
     pl.off_h = take(sizeof(float) * pl.f);
@@ -508,8 +507,7 @@ size_t dip_gathered_gemv_workspace_bytes(const dip_weight* w, int32_t k) {
     if (!w || w->n_out < 1 || k < 1) return 0;
     if (w->dtype != DIP_F32 && w->dtype != DIP_BF16 && w->dtype != DIP_INT4_G128) return 0;
     const GemvShape s = choose_gemv_shape(w->dtype, w->n_out, 1, k);
-    const int strips = gemv_strips(s, w->dtype, w->n_out);
-    size_t bytes = align_up(sizeof(uint64_t) * strips, 256);
+    size_t bytes = align_up(ticket_bytes(gemv_strips(s, w->dtype, w->n_out)), 256);
     bytes += 2 * align_up(sizeof(float) * (size_t)k, 256);   // aligned copies of idx and x[idx]
     if (s.ksplit > 1) bytes += align_up(sizeof(float) * (size_t)w->n_out * s.ksplit, 256);
     return bytes;
@@ -525,11 +523,10 @@ int32_t dip_gathered_gemv(const dip_weight* w, const float* x, const int32_t* id
     if (!ws || ws_bytes < need || !aligned(ws, 256))
         return fail(DIP_ERR_WORKSPACE, "dip_gathered_gemv: workspace must be 256-aligned and >= %zu bytes", need);
     const GemvShape s = choose_gemv_shape(w->dtype, w->n_out, 1, k);
-    const int strips = gemv_strips(s, w->dtype, w->n_out);
     hipStream_t hs = static_cast<hipStream_t>(stream);
     char* base = static_cast<char*>(ws);
     uint64_t* counters = reinterpret_cast<uint64_t*>(base);
-    size_t o = align_up(sizeof(uint64_t) * strips, 256);
+    size_t o = align_up(ticket_bytes(gemv_strips(s, w->dtype, w->n_out)), 256);
     int32_t* idx_copy = reinterpret_cast<int32_t*>(base + o);
     o += align_up(sizeof(float) * (size_t)k, 256);
     float* val = reinterpret_cast<float*>(base + o);
@@ -1023,7 +1020,6 @@ namespace {
 struct PartialPlan {
     int d, f;
     GemvShape dense, dn;
-    int strips_dense, strips_dn;
     size_t off_a, off_idx, off_hsel, off_part_dense, off_part_dn, off_cnt, total;
 };
 PartialPlan plan_partial(const dip_mlp_split* mlp, int k) {
@@ -1032,8 +1028,6 @@ PartialPlan plan_partial(const dip_mlp_split* mlp, int k) {
     pl.f = mlp->w_dense.n_out;
     pl.dense = choose_gemv_shape(mlp->w_dense.dtype, pl.f, 1, pl.d);
     pl.dn = choose_gemv_shape(mlp->w_d.dtype, pl.d, 1, k);
-    pl.strips_dense = gemv_strips(pl.dense, mlp->w_dense.dtype, pl.f);
-    pl.strips_dn = gemv_strips(pl.dn, mlp->w_d.dtype, pl.d);
     size_t o = 0;
     auto take = [&](size_t bytes) { size_t at = o; o = align_up(o + bytes, 256); return at; };
     pl.off_a = take(sizeof(float) * pl.f);
@@ -1041,7 +1035,7 @@ PartialPlan plan_partial(const dip_mlp_split* mlp, int k) {
     pl.off_hsel = take(sizeof(float) * k);
     pl.off_part_dense = take(pl.dense.ksplit > 1 ? sizeof(float) * pl.f * pl.dense.ksplit : 0);
     pl.off_part_dn = take(pl.dn.ksplit > 1 ? sizeof(float) * pl.d * pl.dn.ksplit : 0);
-    pl.off_cnt = take(sizeof(uint64_t) * std::max(pl.strips_dense, pl.strips_dn));
+    pl.off_cnt = take(sizeof(uint64_t) * kTicketWords);
     pl.total = o;
     return pl;
 }
@@ -1271,6 +1265,7 @@ int32_t dip_tiered_mlp_forward(const dip_tiered_mlp* mlp, const float* x, int32_
         tp.evicted = evw; tp.inserted = insw; tp.meta = cache->meta; tp.n = n; tp.capacity = tw.capacity;
         tp.slot_of = tw.slot_of; tp.fill_col = fcol; tp.fill_slot = fslot; tp.fill_count = fcnt;
         tp.idx = idx[pt]; tp.k = k; tp.src = src;
+        tp.counters = counters; tp.epoch = next_epoch();
         if ((st = check_hip(launch_tier_update(tp, hs), "tier update"))) return st;
         TierFillParams fp;
         fp.host_rows = tw.full.data; fp.slots = tw.slots; fp.row_stride = tw.full.row_stride_bytes;
@@ -1286,12 +1281,12 @@ int32_t dip_tiered_mlp_forward(const dip_tiered_mlp* mlp, const float* x, int32_
         g.idx = src; g.val = val[pt]; g.k = k;
         if (pt == 0) {
             g.n_out = pl.f; g.nseg = 2; g.out = h;
-            g.partial = reinterpret_cast<float*>(base + pl.off_part_ug); g.counters = counters;
+            g.partial = reinterpret_cast<float*>(base + pl.off_part_ug); g.counters = counters; g.epoch = tp.epoch;
             // (the launch shapes of dip_swiglu_mlp_forward: the same sums in the same order)
             st = check_hip(launch_gemv(g, pl.fuse_ug ? pl.fug : pl.ug, hs, DIP_KERNEL_GEMV_UPGATE), "gathered GEMV (up/gate)");
         } else {
             g.n_out = pl.d; g.nseg = 1; g.out = y_out;
-            g.partial = reinterpret_cast<float*>(base + pl.off_part_dn); g.counters = counters;
+            g.partial = reinterpret_cast<float*>(base + pl.off_part_dn); g.counters = counters; g.epoch = tp.epoch;
             st = check_hip(launch_gemv(g, pl.fuse_dn ? pl.fdn : pl.dn, hs, DIP_KERNEL_GEMV_DOWN), "gathered GEMV (down)");
         }
         if (st) return st;

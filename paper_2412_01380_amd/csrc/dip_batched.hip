@@ -17,6 +17,8 @@
 //   breduce_kernel   adds the partial sums in share order and applies the epilogue
 //                    (SwiGLU for the bundled up/gate matrix, Sec. 3 Eq. 2)
 
+#include <algorithm>
+
 #include "dip_internal.h"
 #include "dip_select_device.h"
 
@@ -247,8 +249,8 @@ __device__ __forceinline__ void load_mult(const float* p, float (&m)[B]) {
 constexpr int kBWaves = 4;
 constexpr int kBUnroll = 4;   // listed columns in flight per lane group
 
-template <int DT, int B>
-__global__ __launch_bounds__(kBWaves * 64) void bgemv_kernel(BatchedGemvParams p) {
+template <int DT, int B, int LAYERS>
+__global__ __launch_bounds__(kBWaves * 64) void bgemv_kernel(BatchedGemvParamsT<LAYERS> p) {
     using E = typename BPick<DT, B>::type;
     constexpr int EPL = E::kElems;
     constexpr int LPR = E::kLanes;
@@ -265,7 +267,7 @@ __global__ __launch_bounds__(kBWaves * 64) void bgemv_kernel(BatchedGemvParams p
     // lanes past the right edge of a ragged last strip re-read its last piece; they own no output
     const int col = col_raw < p.n_out ? col_raw : p.n_out - EPL;
 
-    const int layer = blockIdx.z;
+    const int layer = LAYERS == 1 ? 0 : blockIdx.z;
     // (the parameters stay untouched: a table in them indexed by the layer is read from where it
     //  is only as long as nothing writes to them)
     const int32_t* uidx = p.uidx + layer * p.list_layer_stride;
@@ -449,8 +451,8 @@ struct MfmaShared {
     };
 };
 
-template <int KW>
-__global__ __launch_bounds__(kMWaves * 64, 2) void bgemv_q4_mfma_kernel(BatchedGemvParams p) {
+template <int KW, int LAYERS>
+__global__ __launch_bounds__(kMWaves * 64, 2) void bgemv_q4_mfma_kernel(BatchedGemvParamsT<LAYERS> p) {
     typedef MfmaShared<KW> SH;
     constexpr int CW = kMWaves / KW, STRIP = kMWaveCols * CW;
     __shared__ __align__(16) SH sh;
@@ -461,7 +463,7 @@ __global__ __launch_bounds__(kMWaves * 64, 2) void bgemv_q4_mfma_kernel(BatchedG
     const int B = p.batch;
     const int ngroups = p.n_out >> 7;
 
-    const int layer = blockIdx.z;
+    const int layer = LAYERS == 1 ? 0 : blockIdx.z;
     const int32_t* uidx = p.uidx + layer * p.list_layer_stride;
     const float* uval = p.uval + layer * p.list_layer_stride * B;
     const uint32_t* rowmax = p.rowmax + 8 * layer;
@@ -658,52 +660,68 @@ __global__ __launch_bounds__(kMWaves * 64, 2) void bgemv_q4_mfma_kernel(BatchedG
 // reads of the sums; their number per lane is that of the shares (a fixed 20 in flight, the spare
 // ones re-reading the last share, took 49 us for two shares of 40 layers of the Phi-3-Medium
 // shape at 8 rows, where two in flight and 16 bytes per lane take 19 us).
-template <int V, int FLIGHT>
+template <bool GLU, int V, int FLIGHT>
 __global__ __launch_bounds__(256) void breduce_kernel(BatchedReduceParams p) {
     typedef float vec __attribute__((ext_vector_type(V)));
     const int j = (blockIdx.x * 256 + threadIdx.x) * V;
     const int b = blockIdx.y;
-    const int width = p.glu ? p.n_out / 2 : p.n_out;
+    const int width = GLU ? p.n_out / 2 : p.n_out;
     if (j >= width) return;
     const size_t gstride = (size_t)p.batch * (size_t)p.n_out;
     const float* src = p.partial + blockIdx.z * p.partial_layer_stride + (size_t)b * (size_t)p.n_out + j;
-    auto sum = [&](const float* q) {
-        vec s = vec(0.f);
-        for (int g0 = 0; g0 < p.shares; g0 += FLIGHT) {
-            vec a[FLIGHT];
-            // (loads past the last share re-read it and are dropped: a load under a branch would be
-            //  waited for where the branch ends, one round trip each)
+    vec s = vec(0.f), gate = vec(0.f);
+    for (int g0 = 0; g0 < p.shares; g0 += FLIGHT) {
+        vec a[FLIGHT], b[FLIGHT];
+        // (loads past the last share re-read it and are dropped: a load under a branch would be
+        //  waited for where the branch ends, one round trip each)
 #pragma unroll
-            for (int i = 0; i < FLIGHT; ++i)
-                a[i] = *reinterpret_cast<const vec*>(q + (size_t)min(g0 + i, p.shares - 1) * gstride);
-#pragma unroll
-            for (int i = 0; i < FLIGHT; ++i)
-                if (g0 + i < p.shares) s += a[i];
+        for (int i = 0; i < FLIGHT; ++i) {
+            const float* q = src + (size_t)min(g0 + i, p.shares - 1) * gstride;
+            a[i] = *reinterpret_cast<const vec*>(q);
+            if constexpr (GLU) b[i] = *reinterpret_cast<const vec*>(q + width);
         }
-        return s;
-    };
-    vec s = sum(src);
-    if (p.glu) {
-        const vec gate = sum(src + width);
+#pragma unroll
+        for (int i = 0; i < FLIGHT; ++i)
+            if (g0 + i < p.shares) {
+                s += a[i];
+                if constexpr (GLU) gate += b[i];
+            }
+    }
+    if constexpr (GLU) {
 #pragma unroll
         for (int v = 0; v < V; ++v) s[v] = s[v] * (gate[v] / (1.0f + expf(-gate[v])));
     }
     *reinterpret_cast<vec*>(p.out + blockIdx.z * p.out_layer_stride + (size_t)b * p.out_stride + j) = s;
 }
 
-template <int DT>
-hipError_t launch_dt(const BatchedGemvParams& p, dim3 grid, hipStream_t stream, int pk) {
+template <int DT, int LAYERS>
+hipError_t launch_dt(const BatchedGemvParamsT<LAYERS>& p, dim3 grid, hipStream_t stream, int pk) {
     const dim3 block(kBWaves * 64);
     switch (p.batch) {
-        case 1: return launch_timed(bgemv_kernel<DT, 1>, grid, block, stream, pk, p);
-        case 2: return launch_timed(bgemv_kernel<DT, 2>, grid, block, stream, pk, p);
-        case 3: return launch_timed(bgemv_kernel<DT, 3>, grid, block, stream, pk, p);
-        case 4: return launch_timed(bgemv_kernel<DT, 4>, grid, block, stream, pk, p);
-        case 5: return launch_timed(bgemv_kernel<DT, 5>, grid, block, stream, pk, p);
-        case 6: return launch_timed(bgemv_kernel<DT, 6>, grid, block, stream, pk, p);
-        case 7: return launch_timed(bgemv_kernel<DT, 7>, grid, block, stream, pk, p);
-        case 8: return launch_timed(bgemv_kernel<DT, 8>, grid, block, stream, pk, p);
+        case 1: return launch_timed(bgemv_kernel<DT, 1, LAYERS>, grid, block, stream, pk, p);
+        case 2: return launch_timed(bgemv_kernel<DT, 2, LAYERS>, grid, block, stream, pk, p);
+        case 3: return launch_timed(bgemv_kernel<DT, 3, LAYERS>, grid, block, stream, pk, p);
+        case 4: return launch_timed(bgemv_kernel<DT, 4, LAYERS>, grid, block, stream, pk, p);
+        case 5: return launch_timed(bgemv_kernel<DT, 5, LAYERS>, grid, block, stream, pk, p);
+        case 6: return launch_timed(bgemv_kernel<DT, 6, LAYERS>, grid, block, stream, pk, p);
+        case 7: return launch_timed(bgemv_kernel<DT, 7, LAYERS>, grid, block, stream, pk, p);
+        case 8: return launch_timed(bgemv_kernel<DT, 8, LAYERS>, grid, block, stream, pk, p);
     }
+    return hipErrorInvalidValue;
+}
+
+template <int LAYERS>
+hipError_t launch_product(const BatchedGemvParamsT<LAYERS>& p, bool mc, int kw, dim3 grid, hipStream_t stream, int pk) {
+    if (mc) {
+        if (!p.rowmax || p.dtype != DIP_INT4_G128 || (int64_t)p.n_in * p.row_stride >= ((int64_t)1 << 32))
+            return hipErrorInvalidValue;
+        const dim3 block(kMWaves * 64);
+        if (kw == 1) return launch_timed(bgemv_q4_mfma_kernel<1, LAYERS>, grid, block, stream, pk, p);
+        return launch_timed(bgemv_q4_mfma_kernel<kMWaves, LAYERS>, grid, block, stream, pk, p);
+    }
+    if (p.dtype == DIP_F32) return launch_dt<DIP_F32>(p, grid, stream, pk);
+    if (p.dtype == DIP_BF16) return launch_dt<DIP_BF16>(p, grid, stream, pk);
+    if (p.dtype == DIP_INT4_G128) return launch_dt<DIP_INT4_G128>(p, grid, stream, pk);
     return hipErrorInvalidValue;
 }
 
@@ -727,8 +745,7 @@ static BatchedShape batched_shape(int dtype, int n_out, int k_max, bool mc, int 
         const int strips = (n_out + sc - 1) / sc * layers;
         int g = (1024 + strips - 1) / strips;
         if (layers > 1 && g < (k_max + kLong - 1) / kLong) g = (k_max + kLong - 1) / kLong;
-        while (g > 1 && k_max / g < 32) --g;
-        return {sc, 1, g < 1 ? 1 : g};
+        return {sc, 1, std::max(1, std::min(g, k_max / 32))};
     }
     // Matrix-core product, two workgroups to a compute unit.  Wavefronts side by side stage the
     // list once for 1024 stored columns and add nothing across wavefronts; taken where five rounds
@@ -737,15 +754,13 @@ static BatchedShape batched_shape(int dtype, int n_out, int k_max, bool mc, int 
     // Phi-3-Medium shape, 40 layers, 8 rows) take 85 of 444 us.
     constexpr int kWide = kMWaves * kMWaveCols;
     const int wide = (n_out + kWide - 1) / kWide * layers;
-    int g = (5 * 512 + wide - 1) / wide;
-    while (g > 1 && k_max / g < kMChunk) --g;
+    int g = std::max(1, std::min((5 * 512 + wide - 1) / wide, k_max / kMChunk));
     if ((int64_t)wide * g >= 1024) return {kWide, 1, g};
     // One round of workgroups whose wavefronts take the sets of a narrow strip in turn, at least
     // one set of 32 per wavefront.
     const int strips = (n_out + kMWaveCols - 1) / kMWaveCols * layers;
-    g = 512 / strips;
-    while (g > 1 && k_max / g < kMWaves * kMRowSet) --g;
-    return {kMWaveCols, kMWaves, g < 1 ? 1 : g};
+    g = std::max(1, std::min(512 / strips, k_max / (kMWaves * kMRowSet)));
+    return {kMWaveCols, kMWaves, g};
 }
 
 int batched_shares(int dtype, int n_out, int k_max, bool mc, int layers) {
@@ -764,26 +779,18 @@ hipError_t launch_batched_gemv(const BatchedGemvParams& p, int shares, bool mc, 
     const BatchedShape shape = batched_shape(p.dtype, p.n_out, p.k_max, mc, layers);
     dim3 grid((p.n_out + shape.strip - 1) / shape.strip, shares, layers);
     if (layers < 1 || layers > kStackLayers) return hipErrorInvalidValue;
-    if (mc) {
-        if (!p.rowmax || p.dtype != DIP_INT4_G128 || (int64_t)p.n_in * p.row_stride >= ((int64_t)1 << 32))
-            return hipErrorInvalidValue;
-        const dim3 block(kMWaves * 64);
-        if (shape.kw == 1) return launch_timed(bgemv_q4_mfma_kernel<1>, grid, block, stream, pk, p);
-        return launch_timed(bgemv_q4_mfma_kernel<kMWaves>, grid, block, stream, pk, p);
-    }
-    if (p.dtype == DIP_F32) return launch_dt<DIP_F32>(p, grid, stream, pk);
-    if (p.dtype == DIP_BF16) return launch_dt<DIP_BF16>(p, grid, stream, pk);
-    if (p.dtype == DIP_INT4_G128) return launch_dt<DIP_INT4_G128>(p, grid, stream, pk);
-    return hipErrorInvalidValue;
+    if (layers == 1) return launch_product(one_layer(p), mc, shape.kw, grid, stream, pk);
+    return launch_product(p, mc, shape.kw, grid, stream, pk);
 }
 
-template <int V>
+template <bool GLU, int V>
 static hipError_t launch_reduce(const BatchedReduceParams& p, int layers, hipStream_t stream) {
-    const int width = p.glu ? p.n_out / 2 : p.n_out;
+    const int width = GLU ? p.n_out / 2 : p.n_out;
     const dim3 grid((width + 256 * V - 1) / (256 * V), p.batch, layers), block(256);
-    if (p.shares <= 2) hipLaunchKernelGGL((breduce_kernel<V, 2>), grid, block, 0, stream, p);
-    else if (p.shares <= 6) hipLaunchKernelGGL((breduce_kernel<V, 6>), grid, block, 0, stream, p);
-    else hipLaunchKernelGGL((breduce_kernel<V, 20>), grid, block, 0, stream, p);
+    constexpr int kMost = GLU && V > 1 ? 12 : 20;      // (96 and 40 or 80 registers)
+    if (p.shares <= 2) hipLaunchKernelGGL((breduce_kernel<GLU, V, 2>), grid, block, 0, stream, p);
+    else if (p.shares <= 6) hipLaunchKernelGGL((breduce_kernel<GLU, V, 6>), grid, block, 0, stream, p);
+    else hipLaunchKernelGGL((breduce_kernel<GLU, V, kMost>), grid, block, 0, stream, p);
     return hipGetLastError();
 }
 
@@ -795,7 +802,8 @@ hipError_t launch_batched_reduce(const BatchedReduceParams& p, int layers, hipSt
                      p.out_layer_stride % 4 == 0 &&
                      ((reinterpret_cast<uintptr_t>(p.partial) | reinterpret_cast<uintptr_t>(p.out)) & 15) == 0 &&
                      (int64_t)width * p.batch * layers >= 128 * 1024;
-    return vec ? launch_reduce<4>(p, layers, stream) : launch_reduce<1>(p, layers, stream);
+    if (p.glu) return vec ? launch_reduce<true, 4>(p, layers, stream) : launch_reduce<true, 1>(p, layers, stream);
+    return vec ? launch_reduce<false, 4>(p, layers, stream) : launch_reduce<false, 1>(p, layers, stream);
 }
 
 }  // namespace dip

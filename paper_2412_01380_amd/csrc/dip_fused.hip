@@ -81,7 +81,6 @@ __global__ __launch_bounds__(kSelThreads) void fused_kernel(FusedParams fp) {
     int phase = 0;
 
     // ---- head: Alg. 1 steps 1-2 on q.v --------------------------------------------------------
-    const uint64_t seen = ticket_peek(p, strip, G);
     float v[ITEMS];
     uint32_t key[ITEMS];
     const int mine_n = q.n > tid ? (q.n - tid - 1) / kSelThreads + 1 : 0;
@@ -89,7 +88,6 @@ __global__ __launch_bounds__(kSelThreads) void fused_kernel(FusedParams fp) {
     float M;
     uint32_t K_lo, K_hi;    // keys in [K_lo, K_hi) tie at the k-th largest score, keys >= K_hi lie above it
     head_threshold<ITEMS>(q.v, q.n, (uint32_t)p.k, q.score_bits, q.gamma, hs, phase, v, key, M, K_lo, K_hi);
-    ticket_open(p, strip, seen);
 
     // ---- this workgroup's share of the list ---------------------------------------------------
     // Counts of the keys >= K_lo per (slot, wavefront) tile and their running sums in index

@@ -41,10 +41,8 @@ __global__ __launch_bounds__(WAVES * 64) void gemv_kernel(GemvParams p) {
     // this workgroup's share of the selected rows
     const int kb = min(p.k, g * p.rows_per_split);   // rows_per_split is a multiple of 8
     const int ke = min(p.k, kb + p.rows_per_split);
-    const uint64_t seen = ticket_peek(p, strip, G);
     float acc[NSEG][T::EPL];
     accumulate<WT, LPR, WAVES, UNROLL, NSEG>(p, p.idx, p.val, 0, kb, ke, strip, acc);
-    ticket_open(p, strip, seen);
     finish<WT, LPR, WAVES, UNROLL, NSEG>(p, acc, strip, g, G, red, s_last);
 }
 
@@ -65,13 +63,11 @@ __global__ __launch_bounds__(kGatherWaves * 64) void gemv_gather_kernel(GemvPara
     const int g = blockIdx.y, G = gridDim.y;
     const int kb = min(p.k, g * p.rows_per_split);   // rows_per_split is a multiple of 8, <= kGatherCap
     const int ke = min(p.k, kb + p.rows_per_split);
-    const uint64_t seen = ticket_peek(p, strip, G);
     for (int t = threadIdx.x; t < ke - kb; t += kGatherWaves * 64) {
         const int r = p.idx[kb + t];
         l_idx[t] = r;
         l_val[t] = (unsigned)r < (unsigned)p.n_in ? x[r] : 0.f;
     }
-    ticket_open(p, strip, seen);
     __syncthreads();
     float acc[1][T::EPL];
     accumulate<WT, kGatherLpr, kGatherWaves, kGatherUnroll, 1>(p, l_idx, l_val, kb, kb, ke, strip, acc);
@@ -469,7 +465,7 @@ uint64_t next_epoch() {
 
 hipError_t launch_gemv(const GemvParams& p0, const GemvShape& s, hipStream_t stream, int pk) {
     GemvParams p = p0;
-    p.epoch = next_epoch();
+    if (!p.epoch) p.epoch = next_epoch();
     p.rows_per_split = ((p.k + s.ksplit - 1) / s.ksplit + 7) / 8 * 8;   // keeps vector index loads aligned
     if (p.dtype == DIP_F32) return launch_lpr<float>(p, s, stream, pk);
     if (p.dtype == DIP_BF16) return launch_lpr<uint16_t>(p, s, stream, pk);

@@ -131,11 +131,39 @@ struct Tile {
     static constexpr int NOUT = NSEG * SC;           // outputs a workgroup owns
 };
 
+// Ticket counters.  A counter word is the tag of a launch (upper 48 bits, different for every
+// launch of every call) and the tickets drawn in it (lower 16 bits), so that nothing has to clear
+// the words in front of a launch -- a launch of its own, 3 us of a 31 us layer: a word with
+// another tag, whatever wrote it, counts as no tickets.  Every workgroup looks at its word early
+// (peek: not ahead of loads it waits for, which return in order and would wait for this one from
+// behind the caches) and, if the tag is not this launch's, swaps the word it saw for (tag, 0) before it
+// draws its own ticket (open: not in front of a barrier, which would wait for it); the swap fails if another workgroup was faster, and then the tag
+// is in place already.  The last ticket holder leaves (tag, 0).  peek returns what thread 0 saw.
+// The words of the first 64 strips lie 128 bytes apart: atomics on one line are served one after the
+// other, and all workgroups of a launch come for their word at about the same time.
+__device__ __forceinline__ int ticket_word(int strip) {
+    return strip < kTicketWords ? (strip & 63) * 16 + (strip >> 6) : strip;
+}
+static_assert(kTicketWords == 64 * 16, "one word per strip");
+__device__ __forceinline__ uint64_t ticket_peek(const GemvParams& p, int strip, int G) {
+    uint64_t seen = p.epoch;
+    if (G > 1 && threadIdx.x == 0)
+        seen = __hip_atomic_load(&p.counters[ticket_word(strip)], __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+    return seen;
+}
+__device__ __forceinline__ void ticket_open(const GemvParams& p, int strip, uint64_t seen) {
+    if ((seen ^ p.epoch) >> 16)
+        __hip_atomic_compare_exchange_strong(&p.counters[ticket_word(strip)], &seen, p.epoch, __ATOMIC_RELAXED, __ATOMIC_RELAXED,
+                                             __HIP_MEMORY_SCOPE_AGENT);
+}
+
 // Sum of val[t] * row idx[t] over the list positions [kb, ke) for this lane's 16 bytes of
 // the strip (both segments of a bundled matrix).  The lists are read at position t - list_base:
 // they are either the launch-wide lists in global memory (list_base = 0) or this workgroup's
 // share of them in LDS (list_base = kb).  idx == nullptr means rows kb .. ke-1 themselves (a
 // dense product).  kb - list_base must be a multiple of 4 and the lists 16-byte aligned.
+// The workgroup's ticket counter is looked at once the first pairs are there, before the first
+// weights are requested, and opened behind the first weights: neither waits for the other.
 template <typename WT, int LPR, int WAVES, int UNROLL, int NSEG>
 __device__ __forceinline__ void accumulate(const GemvParams& p, const int32_t* idx, const float* val,
                                            int list_base, int kb, int ke, int strip,
@@ -216,6 +244,7 @@ __device__ __forceinline__ void accumulate(const GemvParams& p, const int32_t* i
     auto fetch_full = [&](int t) { fetch_pairs(t, row, xv); settle_pairs(row, xv, alt); };
 
     if (n_full > 0) fetch_full(t0);
+    const uint64_t seen = ticket_peek(p, strip, gridDim.y);
     for (int it = 0; it < n_full; ++it) {
         typename Elem<WT>::raw_t q[UNROLL][NSEG];
         uint16_t sc[UNROLL][NSEG];
@@ -249,7 +278,9 @@ __device__ __forceinline__ void accumulate(const GemvParams& p, const int32_t* i
                 for (int e = 0; e < EPL; ++e) acc[s][e] = fmaf(f[e], mult, acc[s][e]);
             }
         }
+        if (it == 0) ticket_open(p, strip, seen);
     }
+    if (n_full == 0) ticket_open(p, strip, seen);
     // Tail: fewer than ROWS_PER_ITER rows are left; rows past the end are skipped.
     if (col_ok && t0 < ke) {
         typename Elem<WT>::raw_t q[UNROLL][NSEG];
@@ -309,25 +340,6 @@ __device__ __forceinline__ void accumulate(const GemvParams& p, const int32_t* i
     }
 }
 
-// Ticket counters.  A counter word is the tag of a launch (upper 48 bits, different for every
-// launch of every call) and the tickets drawn in it (lower 16 bits), so that nothing has to clear
-// the words in front of a launch -- a launch of its own, 3 us of a 31 us layer: a word with
-// another tag, whatever wrote it, counts as no tickets.  Every workgroup looks at its word at its
-// start (peek) and, if the tag is not this launch's, swaps the word it saw for (tag, 0) before it
-// draws its own ticket (open); the swap fails if another workgroup was faster, and then the tag
-// is in place already.  The last ticket holder leaves (tag, 0).  peek returns what thread 0 saw.
-__device__ __forceinline__ uint64_t ticket_peek(const GemvParams& p, int strip, int G) {
-    uint64_t seen = p.epoch;
-    if (G > 1 && threadIdx.x == 0)
-        seen = __hip_atomic_load(&p.counters[strip], __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-    return seen;
-}
-__device__ __forceinline__ void ticket_open(const GemvParams& p, int strip, uint64_t seen) {
-    if ((seen ^ p.epoch) >> 16)
-        __hip_atomic_compare_exchange_strong(&p.counters[strip], &seen, p.epoch, __ATOMIC_RELAXED, __ATOMIC_RELAXED,
-                                             __HIP_MEMORY_SCOPE_AGENT);
-}
-
 // Combine the lanes' sums in a fixed order and write the strip's outputs: lane groups of one
 // wavefront (xor butterfly), wavefronts through `red` in index order, and -- with G > 1
 // workgroups per strip -- the workgroups through p.partial, added in workgroup order by the
@@ -380,10 +392,10 @@ __device__ __forceinline__ void finish(const GemvParams& p, float (&acc)[NSEG][E
         asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
         __syncthreads();
         if (tid == 0) {
-            const uint64_t prev = __hip_atomic_fetch_add(&p.counters[strip], 1ull, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+            const uint64_t prev = __hip_atomic_fetch_add(&p.counters[ticket_word(strip)], 1ull, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
             s_last = prev == p.epoch + (uint64_t)(G - 1);
             // (every ticket is drawn: back to none for a replay of this launch from a graph)
-            if (s_last) __hip_atomic_store(&p.counters[strip], p.epoch, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+            if (s_last) __hip_atomic_store(&p.counters[ticket_word(strip)], p.epoch, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
         }
         __syncthreads();
         if (!s_last) return;

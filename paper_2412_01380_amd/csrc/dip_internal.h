@@ -64,7 +64,11 @@ hipError_t launch_select(const SelectParams& p, hipStream_t stream, int prof_kin
 // ---- selections of several vectors: `rows` per layer, several layers of a stack ----------------
 // layers per launch of the stack kernels: their tables travel in the kernel arguments
 constexpr int kStackLayers = 64;
-struct RowsSelectParams {
+// ... and a launch for one layer carries a table of one: a kernel starts when its arguments have
+// come across from host memory, and 1 KB of table costs every small launch about a microsecond
+// (four calls of one 1024 x 2048 layer, 36 launches: 154 us with full tables, 143 with these).
+template <int LAYERS>
+struct RowsSelectParamsT {
     const float* v;               // vector of (layer, row): v + layer * v_layer_stride + row * v_row_stride
     int64_t v_layer_stride;
     int64_t v_row_stride;
@@ -83,8 +87,16 @@ struct RowsSelectParams {
         const uint32_t* score_bits;   // residency for Eq. 10 scores, or null for |v|
         int k;
         int pad;
-    } layer[kStackLayers];
+    } layer[LAYERS];
 };
+typedef RowsSelectParamsT<kStackLayers> RowsSelectParams;
+// the arguments of a one-layer launch
+template <template <int> class P>
+inline P<1> one_layer(const P<kStackLayers>& p) {
+    P<1> q;
+    __builtin_memcpy(static_cast<void*>(&q), &p, sizeof(q));   // (the table is the last member)
+    return q;
+}
 hipError_t launch_select_rows(const RowsSelectParams& p, int layers, hipStream_t stream, int prof_kind);
 
 // Cache updates of several caches in one launch, one workgroup each (nothing in the token
@@ -111,6 +123,8 @@ struct CacheInitParams {
 hipError_t launch_cache_init(const CacheInitParams& p, hipStream_t stream);
 
 // ---- gathered GEMV -----------------------------------------------------------------------
+constexpr int kTicketWords = 1024;   // a word per strip: DIP_MAX_N columns at the narrowest strip width ...
+inline size_t ticket_bytes(int strips) { return sizeof(uint64_t) * (size_t)(strips > kTicketWords ? strips : kTicketWords); }
 struct GemvShape {
     int lpr;     // lanes per stored row
     int waves;   // wavefronts per workgroup
@@ -133,8 +147,8 @@ struct GemvParams {
     int rows_per_split;       // ceil(k / ksplit), filled in by launch_gemv
     float* out;               // n_out floats (nseg == 2: the GLU output, n_out = d_ff)
     float* partial;           // [ksplit][nseg][n_out] when ksplit > 1
-    uint64_t* counters;       // [strips] when ksplit > 1, whatever they hold (see finish())
-    uint64_t epoch;           // this launch's tag in them, filled in by the launcher
+    uint64_t* counters;       // ticket_bytes() when ksplit > 1, whatever they hold (see ticket_open())
+    uint64_t epoch;           // this launch's tag in them; 0: the launcher fills it in
     int act;                  // nseg == 1 only: 0 writes the sums, 1 writes SiLU of the sums
     const void* w_alt;        // second matrix for list entries r < 0 (stored row ~r), same dtype and
     int n_alt;                // row stride, n_alt rows; null / 0 when there is none
@@ -250,7 +264,8 @@ struct UnionParams {
     int64_t list_layer_stride; // entries (uval: times batch)
     uint32_t* count_out;       // number of listed indices, one word per layer
 };
-struct BatchedGemvParams {
+template <int LAYERS>
+struct BatchedGemvParamsT {
     int64_t row_stride;
     int scale_stride;
     int dtype;
@@ -269,8 +284,9 @@ struct BatchedGemvParams {
     struct Layer {
         const void* w;
         const uint16_t* scales;
-    } layer[kStackLayers];
+    } layer[LAYERS];
 };
+typedef BatchedGemvParamsT<kStackLayers> BatchedGemvParams;
 struct BatchedReduceParams {
     const float* partial;
     int shares;
@@ -303,6 +319,8 @@ struct TierParams {
     const int32_t* idx;        // this token's selected columns (k ascending), or null
     int k;
     int32_t* src;              // [k]: slot s >= 0 of a resident column, ~column otherwise
+    uint64_t* counters;        // kTicketWords ticket counters of the product behind this launch ...
+    uint64_t epoch;            // ... and its tag: put in place here (the product's workgroups need not)
 };
 struct TierFillParams {
     const void* host_rows;     // full matrix, device-accessible host memory

@@ -52,13 +52,13 @@ struct EmitList {
     }
 };
 
-template <int ITEMS, bool LISTS>
-__global__ __launch_bounds__(kSelThreads) void rows_select_kernel(RowsSelectParams p) {
+template <int ITEMS, bool LISTS, int LAYERS>
+__global__ __launch_bounds__(kSelThreads) void rows_select_kernel(RowsSelectParamsT<LAYERS> p) {
     __shared__ __align__(16) RowsShared sh;
     HeadShared& hs = sh.head;
     const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
     const int nwords = (p.n + 31) >> 5;
-    const int row = blockIdx.x, layer = blockIdx.y;
+    const int row = blockIdx.x, layer = LAYERS == 1 ? 0 : blockIdx.y;
     const uint32_t k = (uint32_t)p.layer[layer].k;
     int phase = 0;
 
@@ -110,8 +110,9 @@ __global__ __launch_bounds__(kSelThreads) void rows_select_kernel(RowsSelectPara
 template <int ITEMS>
 hipError_t launch_items(const RowsSelectParams& p, int layers, hipStream_t stream, int pk) {
     const dim3 grid(p.rows, layers), block(kSelThreads);
-    if (p.idx_out) return launch_timed(rows_select_kernel<ITEMS, true>, grid, block, stream, pk, p);
-    return launch_timed(rows_select_kernel<ITEMS, false>, grid, block, stream, pk, p);
+    if (p.idx_out) return launch_timed(rows_select_kernel<ITEMS, true, kStackLayers>, grid, block, stream, pk, p);
+    if (layers == 1) return launch_timed(rows_select_kernel<ITEMS, false, 1>, grid, block, stream, pk, one_layer(p));
+    return launch_timed(rows_select_kernel<ITEMS, false, kStackLayers>, grid, block, stream, pk, p);
 }
 
 }  // namespace

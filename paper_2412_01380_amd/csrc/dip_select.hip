@@ -405,15 +405,17 @@ __global__ __launch_bounds__(kSelThreads) void select_kernel(SelectParams p) {
 }
 
 // pieces per launch: they travel in the kernel arguments (4 KB at most), and 80 is what a stack
-// of 40 layers asks for in one call
-constexpr int kUpdateBatch = 80;
+// of 40 layers asks for in one call; a single layer asks for two, and its launch does not wait for
+// 4 KB to come across from host memory
+constexpr int kUpdateBatch = 80, kUpdateLayer = 2;
+template <int PIECES>
 struct UpdateWork {
-    UpdatePiece piece[kUpdateBatch];
+    UpdatePiece piece[PIECES];
 };
-static_assert(sizeof(UpdateWork) <= 4096, "kernel arguments are limited to 4 KB");
+static_assert(sizeof(UpdateWork<kUpdateBatch>) <= 4096, "kernel arguments are limited to 4 KB");
 
-template <int ITEMS>
-__global__ __launch_bounds__(kSelThreads) void update_batch_kernel(UpdateWork work) {
+template <int ITEMS, int PIECES>
+__global__ __launch_bounds__(kSelThreads) void update_batch_kernel(UpdateWork<PIECES> work) {
     __shared__ SelShared sh;
     const UpdatePiece u = work.piece[blockIdx.x];
     SelectParams p;
@@ -456,8 +458,13 @@ hipError_t launch_items(const SelectParams& p, hipStream_t stream, int prof_kind
 }
 
 template <int ITEMS>
-hipError_t launch_update_items(const UpdateWork& work, int count, hipStream_t stream, int prof_kind) {
-    return launch_timed(update_batch_kernel<ITEMS>, dim3(count), dim3(kSelThreads), stream, prof_kind, work);
+hipError_t launch_update_items(const UpdatePiece* pieces, int count, hipStream_t stream, int prof_kind) {
+    auto go = [&](auto work) {
+        constexpr int N = sizeof(work.piece) / sizeof(work.piece[0]);
+        for (int i = 0; i < N; ++i) work.piece[i] = pieces[i < count ? i : 0];
+        return launch_timed(update_batch_kernel<ITEMS, N>, dim3(count), dim3(kSelThreads), stream, prof_kind, work);
+    };
+    return count <= kUpdateLayer ? go(UpdateWork<kUpdateLayer>()) : go(UpdateWork<kUpdateBatch>());
 }
 
 }  // namespace
@@ -465,21 +472,17 @@ hipError_t launch_update_items(const UpdateWork& work, int count, hipStream_t st
 hipError_t launch_update_batch(const UpdatePiece* pieces, int count, hipStream_t stream, int prof_kind) {
     for (int first = 0; first < count; first += kUpdateBatch) {
         const int m = count - first < kUpdateBatch ? count - first : kUpdateBatch;
-        UpdateWork work;
         int n = 1;
-        for (int i = 0; i < kUpdateBatch; ++i) {
-            work.piece[i] = pieces[first + (i < m ? i : 0)];
-            if (i < m && work.piece[i].n > n) n = work.piece[i].n;
-        }
+        for (int i = 0; i < m; ++i) n = pieces[first + i].n > n ? pieces[first + i].n : n;
         // all pieces of a launch run the instantiation that fits the longest cache
         const int items = (n + kSelThreads - 1) / kSelThreads;
         hipError_t e;
-        if (items <= 4) e = launch_update_items<4>(work, m, stream, prof_kind);
-        else if (items <= 8) e = launch_update_items<8>(work, m, stream, prof_kind);
-        else if (items <= 14) e = launch_update_items<14>(work, m, stream, prof_kind);
-        else if (items <= 18) e = launch_update_items<18>(work, m, stream, prof_kind);
-        else if (items <= 24) e = launch_update_items<24>(work, m, stream, prof_kind);
-        else e = launch_update_items<32>(work, m, stream, prof_kind);
+        if (items <= 4) e = launch_update_items<4>(pieces + first, m, stream, prof_kind);
+        else if (items <= 8) e = launch_update_items<8>(pieces + first, m, stream, prof_kind);
+        else if (items <= 14) e = launch_update_items<14>(pieces + first, m, stream, prof_kind);
+        else if (items <= 18) e = launch_update_items<18>(pieces + first, m, stream, prof_kind);
+        else if (items <= 24) e = launch_update_items<24>(pieces + first, m, stream, prof_kind);
+        else e = launch_update_items<32>(pieces + first, m, stream, prof_kind);
         if (e != hipSuccess) return e;
     }
     return hipSuccess;

@@ -20,6 +20,8 @@
 // scalar; the row of weights is widened once for all of them.
 //
 // int4 rows are a quarter of the bytes and bound by vector instructions: see Q4.
+#include <algorithm>
+
 #include "dip_internal.h"
 
 namespace dip {
@@ -282,9 +284,7 @@ int stack_shares(int dtype, int n_out, int k_max, int layers, int rows) {
     const int wgs = stack_strips(dtype, n_out) * layers;
     // (the sums of a share are written and read once per batch row: longer shares for more rows)
     const int kLong = rows == 1 ? 384 : 1536, target = rows == 1 ? 1024 : 2048, least = rows == 1 ? 64 : 256;
-    int g = (k_max + kLong - 1) / kLong;
-    while (wgs * g < target && k_max / (g + 1) >= least) ++g;
-    return g < 1 ? 1 : g;
+    return std::max((k_max + kLong - 1) / kLong, std::min((target + wgs - 1) / wgs, k_max / least));
 }
 
 hipError_t launch_stack_product(const StackProductParams& p, int dtype, int shares, int layers, hipStream_t stream,

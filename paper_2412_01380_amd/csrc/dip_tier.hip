@@ -84,6 +84,8 @@ __global__ __launch_bounds__(kTierThreads) void tier_update_kernel(TierParams p)
         }
         p.src[t] = code;
     }
+    static_assert(kTierThreads == kTicketWords, "one ticket counter per lane");
+    p.counters[tid] = p.epoch;
 }
 
 constexpr int kFillWaves = 4;

@@ -331,6 +331,22 @@ def test_gathered_gemv_list_forms(D, fmt):
         D.dip_tune_gemv(0, 0, 0, 0)
 
 
+def test_gathered_gemv_more_strips_than_ticket_words(D):
+    """More than 1024 strips and several shares of each: rows longer than any layer's."""
+    n_in, n_out, k = 1100, 64 * 1030 + 8, 1090
+    rng = np.random.default_rng(4)
+    w = (rng.standard_normal((n_in, n_out), dtype=np.float32) * np.float32(0.02))
+    W = D.Weight(dev_weight(w))
+    x = studentt_tokens(1, n_in, seed=4)[0]
+    _, idx = O.topk(np.abs(x), k)
+    ws = workspace(D.dip_gathered_gemv_workspace_bytes(W, k))
+    ws.fill_(0xFF)
+    y = torch.empty(n_out, dtype=torch.float32, device="cuda")
+    for _ in range(2):
+        D.dip_gathered_gemv(W, dev_f32(x), torch.from_numpy(idx.astype(np.int32)).cuda(), k, y, ws)
+        assert_product_close(y.cpu().numpy(), O.gathered_gemv(w, x, idx), "f32", k)
+
+
 # ------------------------------------------------------------------ fused forward, stage replay
 def _stage_replay(D, w, x, k_in, k_mid, tol, cache_pair=None, oracle_caches=None, gamma=0.2):
     """One token through the GPU forward; every stage checked against the oracle applied to
