@@ -294,6 +294,8 @@ int32_t dip_swiglu_mlp_forward_noalloc(const dip_mlp* mlp, const float* x, int32
  * stack): layer l reads x + l * x_stride and writes y_out + l * y_stride (strides in
  * floats) and keeps k_in[l] of its inputs and k_mid[l] of its GLU units (host arrays of
  * n_layers entries: Sec. 4 allows different sparsity levels per matrix and layer).
+ * The layers run phase by phase where their rows lie apart.  If the output of one overlaps the
+ * input of a later one or the output of another, they run one after the other, in order.
  * mlps / caches_in / caches_mid are host arrays of n_layers descriptors; the cache arrays
  * may be NULL (DIP).  Every layer and pruning point needs a dip_cache of its own (the call
  * rejects shared state): all caches are scored in their layers' launches and updated

@@ -323,20 +323,23 @@ size_t stack_scratch(const dip_mlp* mlps, int n_layers, const int32_t* k_in, con
     return need;
 }
 
-// Whether the output of a layer overlaps the input of a later one: a caller may chain layers that
-// way as long as they run one after the other.
-bool stack_chained(const dip_mlp* mlps, int n_layers, int rows, const float* x, int64_t x_stride, const float* y,
+// Whether the layers of a stack have to run one after the other: the output of a layer overlaps the
+// input of a later one (a caller may chain layers that way), or the output of another layer (what
+// stays is the rows of the later layer; the reduction of a phase writes all layers at once).
+bool stack_ordered(const dip_mlp* mlps, int n_layers, int rows, const float* x, int64_t x_stride, const float* y,
                    int64_t y_stride) {
     auto lo = [](const float* p, int64_t s, int n) { return s < 0 ? p + s * (n - 1) : p; };
     auto hi = [](const float* p, int64_t s, int n) { return s < 0 ? p : p + s * (n - 1); };
     int d = 0;
     for (int l = 0; l < n_layers; ++l) d = std::max(d, rows * (int)mlps[l].w_ug.n_in);
-    if (hi(x, x_stride, n_layers) + d <= lo(y, y_stride, n_layers) || hi(y, y_stride, n_layers) + d <= lo(x, x_stride, n_layers))
+    if ((y_stride >= d || y_stride <= -d) &&
+        (hi(x, x_stride, n_layers) + d <= lo(y, y_stride, n_layers) || hi(y, y_stride, n_layers) + d <= lo(x, x_stride, n_layers)))
         return false;
     for (int a = 0; a < n_layers; ++a)
         for (int b = a + 1; b < n_layers; ++b) {
-            const float *yb = y + a * y_stride, *xb = x + b * x_stride;
-            if (yb < xb + rows * mlps[b].w_ug.n_in && xb < yb + rows * mlps[a].w_ug.n_in) return true;
+            const float *ya = y + a * y_stride, *yb = y + b * y_stride, *xb = x + b * x_stride;
+            const int ra = rows * mlps[a].w_ug.n_in, rb = rows * mlps[b].w_ug.n_in;
+            if ((ya < xb + rb && xb < ya + ra) || (ya < yb + rb && yb < ya + ra)) return true;
         }
     return false;
 }
@@ -618,7 +621,7 @@ static int32_t forward_checked(const dip_mlp* mlps, int32_t n_layers, const floa
     std::vector<UpdatePiece> updates;
     updates.reserve(2 * (size_t)n_layers);
     const bool phases = n_layers >= kMinStackLayers && !dbg && !dense_in && g_fusion && !tuned() &&
-                        !stack_chained(mlps, n_layers, 1, x, x_stride, y_out, y_stride);
+                        !stack_ordered(mlps, n_layers, 1, x, x_stride, y_out, y_stride);
     for (int l = 0, m; l < n_layers && !st; l += m) {
         m = phases ? stack_group(mlps, n_layers, l) : 1;
         if (m >= kMinStackLayers) {
@@ -934,9 +937,9 @@ int32_t batched_checked(const dip_mlp* mlps, int n_layers, const float* X, int64
     char* base = static_cast<char*>(ws);
     std::vector<UpdatePiece> updates;
     updates.reserve(2 * (size_t)n_layers);
-    const bool chained = n_layers > 1 && stack_chained(mlps, n_layers, batch, X, x_stride, Y, y_stride);
+    const bool ordered = n_layers > 1 && stack_ordered(mlps, n_layers, batch, X, x_stride, Y, y_stride);
     for (int l = 0, m; l < n_layers && !st; l += m) {
-        m = chained ? 1 : stack_group(mlps, n_layers, l);
+        m = ordered ? 1 : stack_group(mlps, n_layers, l);
         st = batched_group(&mlps[l], m, X + (int64_t)l * x_stride, x_stride, batch, k_in + l * k_stride, k_mid + l * k_stride,
                            k_stride, caches_in ? &caches_in[l] : nullptr, caches_mid ? &caches_mid[l] : nullptr, gamma,
                            Y + (int64_t)l * y_stride, y_stride, mask_in_out, h_out, mask_mid_out, base + mask_bytes,

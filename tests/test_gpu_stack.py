@@ -137,3 +137,54 @@ def test_stack_phases_replay_from_a_graph(D, fmt):
         assert torch.equal(ye.view(torch.int32), yg.view(torch.int32)), t
         for a, b in zip(ce[0] + ce[1], cg[0] + cg[1]):
             assert np.array_equal(host_u32(a.bits), host_u32(b.bits)) and a.meta_host() == b.meta_host(), t
+
+
+def _in_order(D, mlps, buf, x_at, x_stride, y_at, y_stride, B, d, k_in, k_mid):
+    """The same call, layer by layer, on `buf`: one-row calls (B = 0) or batched ones."""
+    one = workspace(max(D.dip_swiglu_mlp_forward_workspace_bytes(mlps[0], k_in, k_mid),
+                        D.dip_swiglu_mlp_forward_batched_workspace_bytes(mlps[0], max(B, 1), k_in, k_mid)))
+    for l, m in enumerate(mlps):
+        x, y = buf[x_at + l * x_stride:], buf[y_at + l * y_stride:]
+        if B == 0:
+            D.dip_swiglu_mlp_forward(m, x, k_in, k_mid, None, None, 0.2, y, None, one)
+        else:
+            D.dip_swiglu_mlp_forward_batched(m, x, B, k_in, k_mid, None, None, 0.2, y, None, None, None, one)
+
+
+@pytest.mark.parametrize("B", [0, 1, 3])
+@pytest.mark.parametrize("case", ["one place", "half a row", "half a row down", "one short", "chained", "last row chained",
+                                  "interleaved"])
+def test_stack_layers_with_overlapping_rows_run_in_order(D, case, B):
+    """Outputs that overlap each other or a later layer's inputs, through both stack calls (B = 0:
+    the one-row call): the bits of one call per layer, in order."""
+    d, f, L, k_in, k_mid = 512, 1536, 6, 160, 500
+    rows = max(B, 1)
+    R = rows * d                                         # floats a layer reads and writes
+    x_at, x_stride, far = 0, R, (L + 1) * R
+    y_at, y_stride = {
+        "one place": (far, 0),
+        "half a row": (far, d // 2),
+        "half a row down": (far + L * R, -(d // 2)),
+        "one short": (far, R - 1),                       # one float of the last batch row only
+        "chained": (R, R),                               # y of layer l is x of layer l + 1
+        "last row chained": (2 * R - (rows - 1) * d, 2 * R),
+        "interleaved": (R, 2 * R),                       # [x0 y0 x1 y1 ...]: nothing overlaps
+    }[case]
+    if case in ("last row chained", "interleaved"):
+        x_stride = 2 * R
+    _, mlps = _layers(D, [(d, f)] * L, "bf16")
+    stack = D.MlpStack(mlps)
+    start = dev_f32(ar1_laplace_stream(1, 4 * (L + 1) * R, seed=12)[0])
+    got, want = start.clone(), start.clone()
+    if B == 0:
+        ws = workspace(D.dip_swiglu_mlp_forward_stack_workspace_bytes(stack, k_in, k_mid))
+        D.dip_swiglu_mlp_forward_stack(stack, got[x_at:], x_stride, k_in, k_mid, 0.2, got[y_at:], y_stride, ws)
+    else:
+        ws = workspace(D.dip_swiglu_mlp_forward_batched_stack_workspace_bytes(stack, B, k_in, k_mid))
+        D.dip_swiglu_mlp_forward_batched_stack(stack, got[x_at:], x_stride, B, k_in, k_mid, 0.2, got[y_at:], y_stride, ws)
+    _in_order(D, mlps, want, x_at, x_stride, y_at, y_stride, B, d, k_in, k_mid)
+    torch.cuda.synchronize()
+    if case == "interleaved":                            # runs in phases: the rounding of another split of the sums
+        assert torch.allclose(got, want, rtol=0, atol=4e-6 * float(want.abs().max()))
+    else:
+        assert torch.equal(got.view(torch.int32), want.view(torch.int32))
