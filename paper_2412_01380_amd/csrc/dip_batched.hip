@@ -442,7 +442,7 @@ struct MfmaShared {
     struct Stage {
         int32_t row[kMChunk];                          // stored row ...
         uint32_t off[kMChunk];                         // ... and its byte offset
-        float m[kMaxRows][kMChunk + 4];                // multipliers (0 past the share)
+        float m[kMaxRows][kMChunk + 4];                // multipliers times their row's power of two (0 past the share)
         uint16_t sc[kGroups][kMChunk + 8];             // fp16 scales
     };
     union {
@@ -488,8 +488,12 @@ __global__ __launch_bounds__(kMWaves * 64, 2) void bgemv_q4_mfma_kernel(BatchedG
     // this lane's row of the left operand: batch row c % 8, first term (c < 8) or 2^10 * second
     const int b_lane = min(c & 7, B - 1);
     const bool second = c >= 8;
-    const float m_scale = row_scale_up(rowmax[b_lane]) * (second ? 1024.0f : 1.0f);
+    const float m_scale = second ? 1024.0f : 1.0f;
     const float whole = second ? 1.0f : 0.0f;
+    // the rows' powers of two, on their own: below maxima of 2^-114 they have no room for the 2^10
+    float up[kMaxRows];
+#pragma unroll
+    for (int b = 0; b < kMaxRows; ++b) up[b] = row_scale_up(rowmax[min(b, B - 1)]);
 
     struct Codes { u32x2 q[8]; };
     auto request = [&](int t, Codes& x) {
@@ -568,7 +572,7 @@ __global__ __launch_bounds__(kMWaves * 64, 2) void bgemv_q4_mfma_kernel(BatchedG
                 sh.st.row[t] = live ? row[j] : 0;
                 sh.st.off[t] = live ? (uint32_t)row[j] * row_stride : 0u;
 #pragma unroll
-                for (int b = 0; b < kMaxRows; ++b) sh.st.m[b][t] = live ? m[j][b] : 0.f;
+                for (int b = 0; b < kMaxRows; ++b) sh.st.m[b][t] = live ? m[j][b] * up[b] : 0.f;
             }
         }
         __syncthreads();

@@ -253,3 +253,41 @@ def test_batched_stack_of_many_layers(D, fmt, B):
         D.dip_swiglu_mlp_forward_batched(mlp, X[l], B, k_in[l], k_mid[l], None, None, 0.2, Y1, None, None, None, one)
         torch.cuda.synchronize()
         assert rel_l2(Y[l].cpu().numpy(), Y1.cpu().numpy()) <= 4e-6, (l, k_in[l], k_mid[l])
+
+
+@pytest.mark.parametrize("layers", [1, 64])
+@pytest.mark.parametrize("scale_log2", [-59, -114, -118, -140])
+@pytest.mark.parametrize("B", [3, 8])
+def test_batched_int4_matrix_core_rows_of_tiny_activations(D, B, scale_log2, layers):
+    """Rows whose largest |activation| comes close to the smallest fp32 number, beside ordinary ones:
+    at 2^-59 the GLU output lies near 2^-122 and makes the row of the second product tiny, from 2^-114
+    on that of the first (whose outputs then vanish in the GLU).  One layer runs with the wavefronts of
+    a workgroup in turn, 64 layers with them side by side."""
+    d, f, k_in, k_mid = 1152, 4224, 400, 1300
+    w = layer_weights(d, f, seed=39, layer=0, dtype="int4")
+    mlp = D.Mlp(make_weight(D, w["ug"]), make_weight(D, w["d"]))
+    X = np.stack([ar1_laplace_stream(1, d, seed=390 + i)[0] for i in range(layers * B)]).reshape(layers, B, d)
+    X[:, 0] *= np.float32(2.0 ** scale_log2)
+    Y = torch.full((layers, B, d), float("nan"), device="cuda")
+    if layers == 1:
+        ws = workspace(D.dip_swiglu_mlp_forward_batched_workspace_bytes(mlp, B, k_in, k_mid))
+        D.dip_swiglu_mlp_forward_batched(mlp, dev_f32(X), B, k_in, k_mid, None, None, 0.2, Y, None, None, None, ws)
+    else:
+        stack = D.MlpStack([mlp] * layers)
+        ws = workspace(D.dip_swiglu_mlp_forward_batched_stack_workspace_bytes(stack, B, k_in, k_mid))
+        D.dip_swiglu_mlp_forward_batched_stack(stack, dev_f32(X), B * d, B, k_in, k_mid, 0.2, Y, B * d, ws)
+    torch.cuda.synchronize()
+    Yg = Y.cpu().numpy()
+    assert np.all(np.isfinite(Yg))
+    for l in {0, layers - 1}:
+        for b in (0, B - 1):
+            _, idx1 = O.topk(O.score(X[l, b], None, 0.2), k_in)
+            h = O.glu_from_preacts(O.gathered_gemv(w["ug"], X[l, b], idx1))
+            _, idx2 = O.topk(O.score(h, None, 0.2), k_mid)
+            y = O.gathered_gemv(w["d"], h, idx2)
+            if b == 0 and scale_log2 <= -114:
+                assert np.all(Yg[l, b] == 0) and np.all(np.abs(y) < 2.0 ** -149), (l, b)
+            else:
+                # (the matrix-core product's bar; that two columns trade places at the threshold of the second
+                # point because h is rounded otherwise has a chance of about d_ff * 2e-7, 1e-3 per row)
+                assert rel_l2(Yg[l, b], y) <= 2e-4, (l, b)
