@@ -280,7 +280,7 @@ int stack_group(const dip_mlp* mlps, int n_layers, int l) {
 struct StackPlan {
     int d, f, k1max, k2max, g1, g2;
     size_t list1, list2, part;     // entries per layer: index list (and multipliers), partial sums
-    size_t off_idx1, off_val1, off_h, off_idx2, off_val2, off_part, total;
+    size_t off_rmax, off_idx1, off_val1, off_h, off_idx2, off_val2, off_part, total;
 };
 StackPlan plan_stack(const dip_mlp* mlp, const int32_t* k_in, const int32_t* k_mid, int k_stride, int layers) {
     StackPlan pl;
@@ -302,6 +302,7 @@ StackPlan plan_stack(const dip_mlp* mlp, const int32_t* k_in, const int32_t* k_m
     }
     size_t o = 0;
     auto take = [&](size_t words) { size_t at = o; o = align_up(o + 4 * words * layers, 256); return at; };
+    pl.off_rmax = take(8);       // maximum of the layer's vector (a batch has 8 of them)
     pl.off_idx1 = take(pl.list1);
     pl.off_val1 = take(pl.list1);
     pl.off_h = take(pl.f);
@@ -364,6 +365,9 @@ int32_t forward_stack_group(const dip_mlp* mlps, int layers, const float* x, int
         sp.n = w0.n_in; sp.rows = 1; sp.gamma = gamma;
         sp.mask_out = caches ? masks + pt * kMaskWords : nullptr; sp.mask_layer_stride = 2 * kMaskWords;
         sp.idx_out = idx; sp.val_out = val; sp.list_layer_stride = pt == 0 ? pl.list1 : pl.list2;
+        // max |v|, for the int4 product's scaling
+        uint32_t* rmax = reinterpret_cast<uint32_t*>(ws + pl.off_rmax);
+        sp.rowmax_out = w0.dtype == DIP_INT4_G128 ? rmax : nullptr; sp.rowmax_layer_stride = 8;
         for (int l = 0; l < layers; ++l) {
             sp.layer[l].k = k[l * k_stride];
             sp.layer[l].score_bits = caches ? caches[l].bits : nullptr;
@@ -378,7 +382,7 @@ int32_t forward_stack_group(const dip_mlp* mlps, int layers, const float* x, int
         std::memset(&gp, 0, sizeof(gp));
         gp.row_stride = w0.row_stride_bytes; gp.scale_stride = w0.n_out / 128; gp.n_in = w0.n_in; gp.n_out = w0.n_out;
         gp.idx = idx; gp.val = val; gp.list_layer_stride = sp.list_layer_stride;
-        gp.rows = 1;
+        gp.rows = 1; gp.rowmax = sp.rowmax_out;
         gp.out = part; gp.out_layer_stride = pl.part;
         for (int l = 0; l < layers; ++l) {
             const dip_weight& w = pt == 0 ? mlps[l].w_ug : mlps[l].w_d;
@@ -826,16 +830,16 @@ int32_t batched_group(const dip_mlp* mlps, int layers, const float* X, int64_t x
 
     struct Point {
         const float* v; int64_t v_stride; int n, kmax, words; const int32_t* k; const dip_cache* caches; uint32_t* masks;
-        size_t masks_stride, list; int32_t* uidx; float* uval; int shares; bool mc, st; int select_kind, gemv_kind;
+        size_t masks_stride, list; int32_t* uidx; float* uval; int shares, dtype; bool mc, st; int select_kind, gemv_kind;
     };
     const Point pts[2] = {
         {X, x_stride, pl.d, pl.k1max, pl.wd, k_in, caches_in,
          mask_in_out ? mask_in_out : reinterpret_cast<uint32_t*>(base + pl.off_m1), pl.masks1, pl.list1,
-         reinterpret_cast<int32_t*>(base + pl.off_idx1), reinterpret_cast<float*>(base + pl.off_val1), pl.g1, pl.mc1, pl.st1,
+         reinterpret_cast<int32_t*>(base + pl.off_idx1), reinterpret_cast<float*>(base + pl.off_val1), pl.g1, mlps[0].w_ug.dtype, pl.mc1, pl.st1,
          DIP_KERNEL_SELECT_IN, DIP_KERNEL_GEMV_UPGATE},
         {H, (int64_t)pl.h, pl.f, pl.k2max, pl.wf, k_mid, caches_mid,
          mask_mid_out ? mask_mid_out : reinterpret_cast<uint32_t*>(base + pl.off_m2), pl.masks2, pl.list2,
-         reinterpret_cast<int32_t*>(base + pl.off_idx2), reinterpret_cast<float*>(base + pl.off_val2), pl.g2, pl.mc2, pl.st2,
+         reinterpret_cast<int32_t*>(base + pl.off_idx2), reinterpret_cast<float*>(base + pl.off_val2), pl.g2, mlps[0].w_d.dtype, pl.mc2, pl.st2,
          DIP_KERNEL_SELECT_MID, DIP_KERNEL_GEMV_DOWN}};
     for (int pt = 0; pt < 2; ++pt) {
         const Point& q = pts[pt];
@@ -844,8 +848,8 @@ int32_t batched_group(const dip_mlp* mlps, int layers, const float* X, int64_t x
         std::memset(&sp, 0, sizeof(sp));
         sp.v = q.v; sp.v_layer_stride = q.v_stride; sp.v_row_stride = q.n; sp.n = q.n; sp.rows = batch; sp.gamma = gamma;
         sp.mask_out = q.masks; sp.mask_layer_stride = q.masks_stride; sp.mask_row_stride = q.words;
-        // max |x| per row, for the matrix-core product's scaling
-        sp.rowmax_out = q.mc ? rmax + 8 * layers * pt : nullptr; sp.rowmax_layer_stride = 8;
+        // max |x| per row, for the scaling of the matrix-core product and of the int4 stack product
+        sp.rowmax_out = q.mc || (q.st && q.dtype == DIP_INT4_G128) ? rmax + 8 * layers * pt : nullptr; sp.rowmax_layer_stride = 8;
         for (int l = 0; l < layers; ++l) {
             sp.layer[l].k = q.k[l * k_stride];
             sp.layer[l].score_bits = q.caches ? q.caches[l].bits : nullptr;
@@ -869,6 +873,7 @@ int32_t batched_group(const dip_mlp* mlps, int layers, const float* X, int64_t x
             std::memset(&gp, 0, sizeof(gp));
             gp.row_stride = w0.row_stride_bytes; gp.scale_stride = w0.n_out / 128; gp.n_in = w0.n_in; gp.n_out = w0.n_out;
             gp.idx = q.uidx; gp.val = q.uval; gp.list_layer_stride = q.list; gp.rows = batch;
+            gp.rowmax = sp.rowmax_out;
             gp.k_dev = up.count_out; gp.k_max = q.kmax; gp.out = part; gp.out_layer_stride = pl.part;
             for (int l = 0; l < layers; ++l) {
                 const dip_weight& w = pt == 0 ? mlps[l].w_ug : mlps[l].w_d;

@@ -230,6 +230,7 @@ struct StackProductParams {
     int rows;                 // batch rows, 1 .. 8
     int k_max;                // capacity of the lists
     const uint32_t* k_dev;    // their lengths in device memory, one word per layer, or null: layer[].k
+    const uint32_t* rowmax;   // int4: bit patterns of max |v| per batch row, 8 words per layer
     float* out;               // sums of share g of layer l: out + l * out_layer_stride + (g * rows + row) * n_out
     int64_t out_layer_stride;
     struct Layer {

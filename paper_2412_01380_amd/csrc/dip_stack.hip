@@ -65,11 +65,18 @@ struct Q4 {
     // patterns of two fp16 denormals, (q + 8) * 2^-24 (bits 0-3) or (q + 8) * 2^-20 (bits 4-7),
     // which v_fma_mix_f32 widens exactly while it multiplies and adds in fp32: 6 instructions
     // unpack 8 codes, where a byte conversion per code takes 12.  The factor leaves through the
-    // multiplier (2^12, exact) and the sums (2^12); the offset as -8 * sum of multipliers.
+    // multiplier (times `up`) and the sums (times 2^24 / up), both exact; the offset as -8 * sum
+    // of multipliers.
     typedef u32x2 raw_t;
     static constexpr int kElems = 16, kBits = 4;
     static constexpr bool kScaled = true;
-    static constexpr float kUp = 4096.0f;      // 2^12 on the multiplier and on the sums
+    // `up` for a batch row whose largest |activation| has these bits.  Multipliers and sums move away
+    // from where the caller's numbers lie by 2^12 each, which a row beyond 2^64 (or below 2^-64) has
+    // no room for: 2^0 leaves its multipliers alone and moves the sums down, 2^24 the other way round.
+    __device__ static __forceinline__ float up(uint32_t max_bits) {
+        const int e = (int)(max_bits >> 23) - 127;
+        return e >= 64 ? 1.0f : (e < -64 ? 16777216.0f : 4096.0f);
+    }
     __device__ static __forceinline__ float lo(uint32_t v) {
         const uint16_t b = (uint16_t)v;
         return (float)__builtin_bit_cast(_Float16, b);
@@ -78,7 +85,7 @@ struct Q4 {
         const uint16_t b = (uint16_t)(v >> 16);
         return (float)__builtin_bit_cast(_Float16, b);
     }
-    // m24 = multiplier * 2^12 for codes in bits 0-3 of a half, m20 = multiplier * 2^8 for bits 4-7
+    // m24 = multiplier * up for codes in bits 0-3 of a half, m20 = multiplier * up / 16 for bits 4-7
     template <int B>
     __device__ static __forceinline__ void fma(const raw_t& q, const float (&m24)[B], const float (&m20)[B],
                                                float (&acc)[B][16]) {
@@ -140,6 +147,13 @@ __global__ __launch_bounds__(Shape<B>::kWaves * 64) void stack_product_kernel(St
         for (int e = 0; e < EPL; ++e) acc[b][e] = 0.f;
     }
 
+    float up[B];
+    if constexpr (E::kScaled) {
+        const DIP_CONSTANT uint32_t* rowmax = (const DIP_CONSTANT uint32_t*)(uintptr_t)(p.rowmax + 8 * layer);
+#pragma unroll
+        for (int b = 0; b < B; ++b) up[b] = E::up(rowmax[b]);
+    }
+
     struct Pairs { int r[kBlock]; float m[kBlock][B]; };
     struct Rows { typename E::raw_t q[kBlock]; uint16_t sc[kBlock]; };
     auto fetch = [&](int t, Pairs& b) {
@@ -168,8 +182,8 @@ __global__ __launch_bounds__(Shape<B>::kWaves * 64) void stack_product_kernel(St
             for (int i = 0; i < B; ++i) {
                 const float mult = m[i] * scale;
                 msum[i] += mult;
-                m24[i] = mult * E::kUp;
-                m20[i] = mult * (E::kUp / 16.0f);
+                m24[i] = mult * up[i];
+                m20[i] = mult * (up[i] * 0.0625f);
             }
             E::template fma<B>(q, m24, m20, acc);
         } else {
@@ -226,7 +240,7 @@ __global__ __launch_bounds__(Shape<B>::kWaves * 64) void stack_product_kernel(St
     for (int b = 0; b < B; ++b) {
         if constexpr (E::kScaled) {
 #pragma unroll
-            for (int e = 0; e < EPL; ++e) acc[b][e] = fmaf(-8.0f, msum[b], acc[b][e] * E::kUp);
+            for (int e = 0; e < EPL; ++e) acc[b][e] = fmaf(-8.0f, msum[b], acc[b][e] * (16777216.0f / up[b]));
         }
         if (b > 0) __syncthreads();
 #pragma unroll
@@ -289,7 +303,7 @@ int stack_shares(int dtype, int n_out, int k_max, int layers, int rows) {
 
 hipError_t launch_stack_product(const StackProductParams& p, int dtype, int shares, int layers, hipStream_t stream,
                                 int pk) {
-    if (!p.idx || !p.val || !p.out || layers < 1 || layers > kStackLayers || shares < 1) return hipErrorInvalidValue;
+    if (!p.idx || !p.val || !p.out || (dtype == DIP_INT4_G128 && !p.rowmax) || layers < 1 || layers > kStackLayers || shares < 1) return hipErrorInvalidValue;
     const dim3 grid(stack_strips(dtype, p.n_out), shares, layers),
         block(64 * (p.rows == 1 ? Shape<1>::kWaves : Shape<2>::kWaves));
     if (dtype == DIP_F32) return launch_rows<F32>(p, grid, block, stream, pk);

@@ -8,7 +8,7 @@ import torch
 
 from oracle import dip_oracle as O
 from workloads import ar1_laplace_stream, layer_weights
-from gpu_util import assert_product_close, dev_f32, host_u32, make_weight, workspace
+from gpu_util import assert_product_close, dev_f32, host_u32, make_weight, rel_l2, workspace
 
 pytestmark = pytest.mark.gpu
 
@@ -188,3 +188,35 @@ def test_stack_layers_with_overlapping_rows_run_in_order(D, case, B):
         assert torch.allclose(got, want, rtol=0, atol=4e-6 * float(want.abs().max()))
     else:
         assert torch.equal(got.view(torch.int32), want.view(torch.int32))
+
+
+@pytest.mark.parametrize("B", [0, 1, 2])
+@pytest.mark.parametrize("scale_log2", [62, 0, -60])
+def test_stack_int4_at_both_ends_of_the_fp32_range(D, B, scale_log2):
+    """The int4 product of the stacks keeps its codes as fp16 denormals and moves their factor into
+    multipliers and sums: the GLU outputs here reach 2^125 (largest) and 2^-122 (root mean square),
+    where neither has room for a fixed factor.  Through both stack calls (B = 0: the one-row call)."""
+    d, f, L, k_in, k_mid = 1152, 4224, 64, 400, 4100     # (a batch takes this kernel from so many rows on)
+    (w,), (mlp,) = _layers(D, [(d, f)], "int4")
+    stack = D.MlpStack([mlp] * L)
+    R = max(B, 1)
+    X = np.stack([ar1_laplace_stream(1, d, seed=400 + i)[0] for i in range(L * R)]).reshape(L, R, d)
+    X[:, 0] *= np.float32(2.0 ** scale_log2)
+    Y = torch.full((L, R, d), float("nan"), device="cuda")
+    if B == 0:
+        ws = workspace(D.dip_swiglu_mlp_forward_stack_workspace_bytes(stack, k_in, k_mid))
+        D.dip_swiglu_mlp_forward_stack(stack, dev_f32(X), d, k_in, k_mid, 0.2, Y, d, ws)
+    else:
+        ws = workspace(D.dip_swiglu_mlp_forward_batched_stack_workspace_bytes(stack, B, k_in, k_mid))
+        D.dip_swiglu_mlp_forward_batched_stack(stack, dev_f32(X), B * d, B, k_in, k_mid, 0.2, Y, B * d, ws)
+    torch.cuda.synchronize()
+    Yg = Y.cpu().numpy()
+    for l in (0, L - 1):
+        for b in range(R):
+            _, idx1 = O.topk(O.score(X[l, b], None, 0.2), k_in)
+            with np.errstate(over="ignore", under="ignore"):
+                h = O.glu_from_preacts(O.gathered_gemv(w["ug"], X[l, b], idx1))
+            assert np.all(np.isfinite(h)) and (b > 0 or scale_log2 != 62 or np.abs(h).max() > 2.0 ** 124)
+            _, idx2 = O.topk(O.score(h, None, 0.2), k_mid)
+            # (sums of 4100 terms round to a few 1e-7, at -60 with steps of 2^-149 on 2^-122)
+            assert rel_l2(Yg[l, b], O.gathered_gemv(w["d"], h, idx2)) <= 4e-6, (l, b)
