@@ -259,9 +259,10 @@ int32_t forward_one(const dip_mlp* mlp, const ForwardPlan& pl, const float* x, i
 // products, the reductions, the selections of point 2, the down products and reductions.  A
 // layer on its own is two launches that each wait for a selection and end with a reduction;
 // over a stack those waits are paid once per call.
-// Measured per layer-step: Phi-3-Medium shape, bf16, 40 layers 45.3 us layer by layer, 27.5 us in phases.
-// From this many layers on (the six launches of the phases cost about as much as two or three
-// layers on their own).
+// Measured per layer-step: Phi-3-Medium shape, bf16, 40 layers 45.3 us layer by layer, 27.7 us in phases.
+// Shorter stacks keep the launches of a call per layer, and with them its bits (phases would take
+// 24 us for two or three layers of 512 x 1536 in bf16 where those take 31 and 45, 78 and 106 us of
+// 5120 x 17920 where they take 91 and 136).
 constexpr int kMinStackLayers = 4;
 
 bool same_layout(const dip_weight& a, const dip_weight& b) {
@@ -750,7 +751,7 @@ BatchedPlan plan_batched(const dip_mlp* mlp, int B, const int32_t* k_in, const i
             const int kmax = pt == 0 ? pl.k1max : pl.k2max;
             const bool mc = pt == 0 ? pl.mc1 : pl.mc2;
             g[pt][0] = batched_shares(w[pt]->dtype, w[pt]->n_out, kmax, mc, m);
-            g[pt][1] = mc || m < 4 ? 0 : stack_shares(w[pt]->dtype, w[pt]->n_out, kmax, m, B);
+            g[pt][1] = mc || m < 2 ? 0 : stack_shares(w[pt]->dtype, w[pt]->n_out, kmax, m, B);
         }
         pl.st1 = !pl.mc1 && stack_pays(mlp->w_ug.dtype, 2 * pl.f, pl.k1max, m, B);
         pl.st2 = !pl.mc2 && stack_pays(mlp->w_d.dtype, pl.d, pl.k2max, m, B);

@@ -16,11 +16,17 @@
 // Up and gate halves of a bundled row are just more columns here; the reduction launch behind
 // the product adds the shares and applies SwiGLU.
 //
+// Rounding: sums of short spans of rows are added to the totals, wavefronts and shares in pairs.  In
+// one chain per wavefront the error against 64 bits was up to 3 times that of a layer on its own
+// (40 layers of the Phi-3-Medium shape: bf16 1.2, at 8 rows 1.6, int4 2.1, at 2 rows 3.1 times); in
+// spans it is 0.75 to 1.0 times, for 3 to 5 % more time with int4 rows and none with the others.
+//
 // A small batch reads the union of its rows' lists with one multiplier per batch row, which stay
 // scalar; the row of weights is widened once for all of them.
 //
 // int4 rows are a quarter of the bytes and bound by vector instructions: see Q4.
 #include <algorithm>
+#include <type_traits>
 
 #include "dip_internal.h"
 
@@ -29,6 +35,9 @@ namespace {
 
 typedef unsigned int u32x4 __attribute__((ext_vector_type(4)));
 typedef unsigned int u32x2 __attribute__((ext_vector_type(2)));
+
+template <typename T, T V>
+using Const = std::integral_constant<T, V>;
 
 #define DIP_CONSTANT __attribute__((address_space(4)))
 
@@ -111,16 +120,22 @@ struct Q4 {
 };
 
 // Wavefronts per workgroup and, for each, rows in flight per register set.  With one batch row
-// eight of both; with more, whose sums and multipliers fill registers, four of both, so that a
-// register or two more do not cost eight wavefronts of a compute unit (two rows of int4, 40
-// layers of the Phi-3-Medium shape: 698 us with eight of both, 568 with four).
+// eight of both; with more, whose sums and multipliers fill registers, four of both (eight
+// wavefronts: up to 1.12 times as long, 40 layers of 3072 x 8192 at 8 rows of bf16 1048 against 1013 us).
 template <int B>
 struct Shape { static constexpr int kWaves = B == 1 ? 8 : 4, kBlock = B == 1 ? 8 : 4; };
+
+// Rows per span.  The sums of a span are added up on their own before they join the totals: rounding
+// errors grow with the length of the chains, and a span followed by their number is two short
+// chains in the place of a long one.  The offset of int4 codes makes the sums within a span larger
+// than what they come to: shorter spans.
+template <typename E, int B>
+constexpr int kSpan = E::kScaled ? 4 : (B == 1 ? 8 : 16);
 
 template <typename E, int B>
 __global__ __launch_bounds__(Shape<B>::kWaves * 64) void stack_product_kernel(StackProductParams p) {
     constexpr int EPL = E::kElems, SC = 64 * EPL;
-    constexpr int kWaves = Shape<B>::kWaves, kBlock = Shape<B>::kBlock;
+    constexpr int kWaves = Shape<B>::kWaves, kBlock = Shape<B>::kBlock, SPAN = kSpan<E, B>;
     __shared__ float red[kWaves][SC];
     const int tid = threadIdx.x, lane = tid & 63;
     const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
@@ -139,13 +154,11 @@ __global__ __launch_bounds__(Shape<B>::kWaves * 64) void stack_product_kernel(St
     const DIP_CONSTANT int32_t* idx = (const DIP_CONSTANT int32_t*)(uintptr_t)(p.idx + layer * p.list_layer_stride);
     const DIP_CONSTANT float* val = (const DIP_CONSTANT float*)(uintptr_t)(p.val + layer * p.list_layer_stride * B);
 
-    float acc[B][EPL], msum[B];
+    float acc[B][EPL], tot[B][EPL];
 #pragma unroll
-    for (int b = 0; b < B; ++b) {
-        msum[b] = 0.f;
+    for (int b = 0; b < B; ++b)
 #pragma unroll
-        for (int e = 0; e < EPL; ++e) acc[b][e] = 0.f;
-    }
+        for (int e = 0; e < EPL; ++e) tot[b][e] = 0.f;
 
     float up[B];
     if constexpr (E::kScaled) {
@@ -174,79 +187,161 @@ __global__ __launch_bounds__(Shape<B>::kWaves * 64) void stack_product_kernel(St
             if constexpr (E::kScaled) x.sc[u] = (scales + (size_t)r * (size_t)p.scale_stride)[sgroup];
         }
     };
-    auto multiply_row = [&](const typename E::raw_t& q, uint16_t sc, const float (&m)[B]) {
-        if constexpr (E::kScaled) {
-            const float scale = (float)__builtin_bit_cast(_Float16, sc);
-            float m24[B], m20[B];
+    // Rows times multipliers, N of them from row FIRST of a block.  OPEN: they are the first of a span.
+    // int4 sums start at the offset of the span's codes.
+    auto rows = [&](auto OPEN, auto FIRST, auto N, const auto& m, const auto& x) {
+        static_assert(OPEN || !E::kScaled, "the offset is that of the rows at hand");
+        float mult[N][B];
 #pragma unroll
-            for (int i = 0; i < B; ++i) {
-                const float mult = m[i] * scale;
-                msum[i] += mult;
-                m24[i] = mult * up[i];
-                m20[i] = mult * (up[i] * 0.0625f);
+        for (int b = 0; b < B; ++b) {
+            float sum = 0.f;
+#pragma unroll
+            for (int u = 0; u < N; ++u) {
+                mult[u][b] = m[FIRST + u][b];
+                if constexpr (E::kScaled) {
+                    mult[u][b] *= (float)__builtin_bit_cast(_Float16, x.sc[FIRST + u]);
+                    sum += mult[u][b];
+                }
             }
-            E::template fma<B>(q, m24, m20, acc);
-        } else {
-            E::template fma<B>(q, m, acc);
+            if constexpr (OPEN) {
+                float first = 0.f;
+                if constexpr (E::kScaled) first = sum * (up[b] * (-8.0f / 16777216.0f));
+#pragma unroll
+                for (int e = 0; e < EPL; ++e) acc[b][e] = first;
+            }
+        }
+#pragma unroll
+        for (int u = 0; u < N; ++u) {
+            if constexpr (E::kScaled) {
+                float m24[B], m20[B];
+#pragma unroll
+                for (int b = 0; b < B; ++b) {
+                    m24[b] = mult[u][b] * up[b];
+                    m20[b] = mult[u][b] * (up[b] * 0.0625f);
+                }
+                E::template fma<B>(x.q[FIRST + u], m24, m20, acc);
+            } else {
+                E::template fma<B>(x.q[FIRST + u], mult[u], acc);
+            }
         }
     };
-    auto multiply = [&](const Pairs& b, const Rows& x) {
+    // ... and ends in the totals
+    auto close = [&] {
 #pragma unroll
-        for (int u = 0; u < kBlock; ++u) multiply_row(x.q[u], E::kScaled ? x.sc[u] : (uint16_t)0, b.m[u]);
+        for (int b = 0; b < B; ++b)
+#pragma unroll
+            for (int e = 0; e < EPL; ++e) tot[b][e] += acc[b][e];
+    };
+    // block number POS after the start of a span
+    auto multiply = [&](auto POS, const Pairs& b, const Rows& x) {
+        constexpr int R = SPAN < kBlock ? SPAN : kBlock;
+        static_assert(kBlock <= 2 * R);
+        Const<bool, POS * kBlock % SPAN == 0> opens;
+        rows(opens, Const<int, 0>(), Const<int, R>(), b.m, x);
+        if constexpr ((POS * kBlock + R) % SPAN == 0) close();
+        if constexpr (R < kBlock) {
+            rows(Const<bool, true>(), Const<int, R>(), Const<int, R>(), b.m, x);
+            close();
+        }
     };
 
     // full blocks t = kb + (wave + i * kWaves) * kBlock
     const int n_blocks = (ke - kb) / kBlock;
-    const int mine = n_blocks > wave ? (n_blocks - wave - 1) / kWaves + 1 : 0;
+    int left = n_blocks > wave ? (n_blocks - wave - 1) / kWaves + 1 : 0;
     constexpr int STEP = kWaves * kBlock;
     int t = kb + wave * kBlock;
-    if (mine > 0) {
+    if (left > 0) {
         Pairs pa, pb;
         Rows xa, xb;
         fetch(t, pa);
         request(pa, xa);
-        int left = mine;
-        while (true) {
-            if (left == 1) { multiply(pa, xa); break; }
-            t += STEP;
-            fetch(t, pb);
-            request(pb, xb);
-            multiply(pa, xa);
-            if (left == 2) { multiply(pb, xb); break; }
-            t += STEP;
-            fetch(t, pa);
-            request(pa, xa);
-            multiply(pb, xb);
-            left -= 2;
+        if constexpr (B == 1) {
+            // (every wavefront has a handful of blocks: none is requested twice)
+            static_assert(SPAN <= kBlock);
+            while (true) {
+                if (left == 1) {
+                    multiply(Const<int, 0>(), pa, xa);
+                    break;
+                }
+                t += STEP;
+                fetch(t, pb);
+                request(pb, xb);
+                multiply(Const<int, 0>(), pa, xa);
+                if (left == 2) {
+                    multiply(Const<int, 0>(), pb, xb);
+                    break;
+                }
+                t += STEP;
+                fetch(t, pa);
+                request(pa, xa);
+                multiply(Const<int, 0>(), pb, xb);
+                left -= 2;
+            }
+        } else {
+            // (past the end the last block is requested again and dropped: loads under a branch would
+            // all be waited for where it ends)
+            const int last = t + (left - 1) * STEP;
+            auto next = [&](Pairs& p, Rows& x) {
+                t = min(t + STEP, last);
+                fetch(t, p);
+                request(p, x);
+                __builtin_amdgcn_sched_barrier(0);     // the loads stay ahead of the products they run beside
+            };
+            constexpr int BLOCKS = SPAN / kBlock;
+            static_assert(BLOCKS == 1 || BLOCKS == 4);
+            constexpr int UNROLL = BLOCKS == 1 ? 2 : BLOCKS;
+            for (; left >= UNROLL; left -= UNROLL) {
+                next(pb, xb);
+                multiply(Const<int, 0>(), pa, xa);
+                next(pa, xa);
+                multiply(Const<int, 1>(), pb, xb);
+                if constexpr (BLOCKS == 4) {
+                    next(pb, xb);
+                    multiply(Const<int, 2>(), pa, xa);
+                    next(pa, xa);
+                    multiply(Const<int, 3>(), pb, xb);
+                }
+            }
+            if (left > 0) {
+                if (BLOCKS > 1 && left > 1) next(pb, xb);
+                multiply(Const<int, 0>(), pa, xa);
+                if (BLOCKS == 4 && left > 1) {
+                    if (left > 2) next(pa, xa);
+                    multiply(Const<int, 1>(), pb, xb);
+                    if (left > 2) multiply(Const<int, 2>(), pa, xa);
+                }
+                if (BLOCKS > 1) close();
+            }
         }
     }
     // what is left of the share, fewer than kBlock rows: one wavefront each
     const int rest = kb + n_blocks * kBlock + wave;
     if (rest < ke) {
         const int r0 = idx[rest];
-        float m[B];
+        struct { typename E::raw_t q[1]; uint16_t sc[1]; } x;
+        float m[1][B];
 #pragma unroll
-        for (int i = 0; i < B; ++i) m[i] = val[rest * B + i];
+        for (int i = 0; i < B; ++i) m[0][i] = val[rest * B + i];
         const uint32_t r = (uint32_t)r0 < (uint32_t)p.n_in ? (uint32_t)r0 : 0u;
-        const typename E::raw_t q = __builtin_nontemporal_load(
+        x.q[0] = __builtin_nontemporal_load(
             reinterpret_cast<const typename E::raw_t*>(w + (size_t)r * (size_t)p.row_stride + voff));
-        uint16_t sc = 0;
-        if constexpr (E::kScaled) sc = (scales + (size_t)r * (size_t)p.scale_stride)[sgroup];
-        multiply_row(q, sc, m);
+        if constexpr (E::kScaled) x.sc[0] = (scales + (size_t)r * (size_t)p.scale_stride)[sgroup];
+        rows(Const<bool, true>(), Const<int, 0>(), Const<int, 1>(), m, x);
+        close();
     }
     static_assert(kBlock <= kWaves, "one leftover row per wavefront");
-    // wavefronts through LDS, added in order
+    // wavefronts through LDS, added in pairs
 #pragma unroll
     for (int b = 0; b < B; ++b) {
         if constexpr (E::kScaled) {
 #pragma unroll
-            for (int e = 0; e < EPL; ++e) acc[b][e] = fmaf(-8.0f, msum[b], acc[b][e] * (16777216.0f / up[b]));
+            for (int e = 0; e < EPL; ++e) tot[b][e] *= 16777216.0f / up[b];
         }
         if (b > 0) __syncthreads();
 #pragma unroll
         for (int e = 0; e < EPL; e += 4)
             *reinterpret_cast<float4*>(&red[wave][lane * EPL + e]) =
-                make_float4(acc[b][e], acc[b][e + 1], acc[b][e + 2], acc[b][e + 3]);
+                make_float4(tot[b][e], tot[b][e + 1], tot[b][e + 2], tot[b][e + 3]);
         __syncthreads();
         float* out = p.out + layer * p.out_layer_stride + ((int64_t)g * B + b) * p.n_out;
 #pragma unroll
@@ -254,10 +349,14 @@ __global__ __launch_bounds__(Shape<B>::kWaves * 64) void stack_product_kernel(St
             const int c = c0 + tid;
             const int gcol = strip * SC + c;
             if (c < SC && gcol < p.n_out) {
-                float s = 0.f;
+                float s[kWaves];
 #pragma unroll
-                for (int i = 0; i < kWaves; ++i) s += red[i][c];
-                out[gcol] = s;
+                for (int i = 0; i < kWaves; ++i) s[i] = red[i][c];
+#pragma unroll
+                for (int h = kWaves / 2; h > 0; h /= 2)
+#pragma unroll
+                    for (int i = 0; i < h; ++i) s[i] += s[i + h];
+                out[gcol] = s[0];
             }
         }
     }
@@ -287,17 +386,25 @@ static int stack_strips(int dtype, int n_out) {
 }
 
 bool stack_pays(int dtype, int n_out, int k_max, int layers, int rows) {
-    // Four workgroups fit a compute unit: one round of them with 512 listed columns each.  Below
-    // that the narrower strips of bgemv_kernel fill the chip better (12 layers of 1024 x 3072 in
-    // bf16 at 6 rows: 75 against 89 us per step; 40 of 2048 x 7168 at 8 rows: 557 against 474).
-    if (dtype == DIP_INT4_G128 && rows > 2) return false;
+    // fp32 and bf16: one round of workgroups, four to a compute unit, with 512 listed columns each.
+    // Below that the narrower strips of bgemv_kernel fill the chip better (bf16 at 3 rows, 4 layers of
+    // 2048 x 7168: 70 against 79 us), from twice as many on they are never ahead (bf16 at 8 rows, 40 layers
+    // of 2048 x 7168: 774 against 637 us); in between the two are within 7 % of each other.
+    // int4: bgemv_kernel adds up its codes with their offset in one chain; its error fits the short
+    // shares of a single layer only.
+    if (dtype == DIP_INT4_G128) return layers >= 2 && rows <= 2;
     return layers >= 4 && (int64_t)stack_strips(dtype, n_out) * layers * ((k_max + 511) / 512) >= 1024;
 }
 
 int stack_shares(int dtype, int n_out, int k_max, int layers, int rows) {
     const int wgs = stack_strips(dtype, n_out) * layers;
-    // (the sums of a share are written and read once per batch row: longer shares for more rows)
-    const int kLong = rows == 1 ? 384 : 1536, target = rows == 1 ? 1024 : 2048, least = rows == 1 ? 64 : 256;
+    // Shares of at most kLong columns, which bounds the rounding error as well, and for few layers as many
+    // as make `target` workgroups of at least `least` columns.  The sums of a share are written and read
+    // once per batch row: longer shares for more rows.  Half or twice any of these moves the mean over
+    // sizes of 512 to 5120 and 4 to 40 layers by 0 to 2 % (`least`: int4 at one row 3.5 % at 32, 6.6 % at 256, at
+    // two rows 2.5 and 12 %).
+    constexpr int least = 64;
+    const int kLong = rows == 1 ? 384 : 1536, target = rows == 1 ? 1024 : 2048;
     return std::max((k_max + kLong - 1) / kLong, std::min((target + wgs - 1) / wgs, k_max / least));
 }
 
