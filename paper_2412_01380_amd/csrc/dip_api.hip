@@ -750,7 +750,7 @@ BatchedPlan plan_batched(const dip_mlp* mlp, int B, const int32_t* k_in, const i
         for (int pt = 0; pt < 2; ++pt) {
             const int kmax = pt == 0 ? pl.k1max : pl.k2max;
             const bool mc = pt == 0 ? pl.mc1 : pl.mc2;
-            g[pt][0] = batched_shares(w[pt]->dtype, w[pt]->n_out, kmax, mc, m);
+            g[pt][0] = batched_shares(w[pt]->dtype, w[pt]->n_out, kmax, pt == 0 ? k1 : k2, mc, m);
             g[pt][1] = mc || m < 2 ? 0 : stack_shares(w[pt]->dtype, w[pt]->n_out, kmax, m, B);
         }
         pl.st1 = !pl.mc1 && stack_pays(mlp->w_ug.dtype, 2 * pl.f, pl.k1max, m, B);

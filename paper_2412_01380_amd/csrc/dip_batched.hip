@@ -14,7 +14,7 @@
 //                    row share; the number of listed columns is read from device memory
 //   bgemv_q4_mfma_kernel  the same product for int4 weights and three or more rows, as a
 //                    dense contraction on the matrix cores
-//   breduce_kernel   adds the partial sums in share order and applies the epilogue
+//   breduce_kernel   adds the partial sums of the shares and applies the epilogue
 //                    (SwiGLU for the bundled up/gate matrix, Sec. 3 Eq. 2)
 
 #include <algorithm>
@@ -660,7 +660,7 @@ __global__ __launch_bounds__(kMWaves * 64, 2) void bgemv_q4_mfma_kernel(BatchedG
 
 // out[b][j] = sum over shares of partial[g][b][j]   (glu == 0), or
 // out[b][j] = up * SiLU(gate), up = sum partial[g][b][j], gate = sum partial[g][b][half + j];
-// V outputs per lane, up to FLIGHT shares in flight at a time, added in share order.  Bound: the
+// V outputs per lane, up to FLIGHT shares in flight at a time, added in pairs.  Bound: the
 // reads of the sums; their number per lane is that of the shares (a fixed 20 in flight, the spare
 // ones re-reading the last share, took 49 us for two shares of 40 layers of the Phi-3-Medium
 // shape at 8 rows, where two in flight and 16 bytes per lane take 19 us).
@@ -684,12 +684,22 @@ __global__ __launch_bounds__(256) void breduce_kernel(BatchedReduceParams p) {
             a[i] = *reinterpret_cast<const vec*>(q);
             if constexpr (GLU) b[i] = *reinterpret_cast<const vec*>(q + width);
         }
+        // in pairs (a sum in share order would be the longest chain of additions of the whole product)
 #pragma unroll
-        for (int i = 0; i < FLIGHT; ++i)
-            if (g0 + i < p.shares) {
-                s += a[i];
-                if constexpr (GLU) gate += b[i];
+        for (int i = 1; i < FLIGHT; ++i)
+            if (g0 + i >= p.shares) {
+                a[i] = vec(0.f);
+                if constexpr (GLU) b[i] = vec(0.f);
             }
+#pragma unroll
+        for (int n = FLIGHT; n > 1; n = (n + 1) / 2)
+#pragma unroll
+            for (int i = 0; i < n / 2; ++i) {
+                a[i] += a[n - 1 - i];
+                if constexpr (GLU) b[i] += b[n - 1 - i];
+            }
+        s += a[0];
+        if constexpr (GLU) gate += b[0];
     }
     if constexpr (GLU) {
 #pragma unroll
@@ -739,19 +749,24 @@ bool batched_on_matrix_cores(int dtype, int batch, int64_t n_in, int64_t row_str
 // Launch shape of the product: strip width, wavefronts of a workgroup along the list (matrix-core
 // product) and shares of the list.
 struct BatchedShape { int strip, kw, shares; };
-static BatchedShape batched_shape(int dtype, int n_out, int k_max, bool mc, int layers) {
+static BatchedShape batched_shape(int dtype, int n_out, int k_max, int k_row, bool mc, int layers) {
     if (!mc) {
-        // Vector-ALU product: about 768 workgroups, at least 32 listed columns each; every share's sums
-        // are written and read (four calls of one layer, 1024 against 768 workgroups: bf16 4096 x 14336
-        // at 8 rows 395 against 369 us, int4 5120 x 17920 at 2 rows 286 against 280).  fp32 rows, in strips
-        // of 64 columns, want 1024 (3072 x 8192 at 2 rows: 236 against 241).  Over several layers there are
-        // workgroups enough: shares of at most kLong listed columns keep the last
-        // round short, and every share costs a write and a read of its sums.
-        constexpr int kLong = 512;
+        // Vector-ALU product: about 1024 workgroups, at least 32 listed columns each; every share's sums are
+        // written and read.  bf16 does with 768 (one layer, 1024 against 768: 5120 x 17920 at 8 rows 163
+        // against 148 us) unless a batch row itself selects so many columns that the longer chains
+        // show (from more than kRows on: error 1.03 times at 5120 x 17920, 55 % of the columns); fp32 rows, in
+        // strips of 64 columns, do not (3072 x 8192 at 2 rows: 236 against 241).  Over several layers
+        // there are workgroups enough: shares of at most kLong listed columns keep the last round short.
+        // int4 takes the shares of a layer on its own at any number of layers (the kernel of the
+        // stacks has the small batches, the matrix cores the others: what is left are matrices beyond
+        // 4 GiB): the offset of the codes grows with the share (768 workgroups for one layer: 2 % less
+        // time, 1.1 times the error).
+        constexpr int kLong = 512, kRows = 640;
         const int sc = dtype == DIP_F32 ? 16 * 4 : (dtype == DIP_BF16 ? 16 * 8 : 32 * 16);
+        if (dtype == DIP_INT4_G128) layers = 1;
         const int strips = (n_out + sc - 1) / sc * layers;
-        const int target = dtype == DIP_F32 ? 1024 : 768;
-        int g = (target + strips - 1) / strips;
+        int g = (768 + strips - 1) / strips;
+        if (dtype != DIP_BF16 || (layers == 1 && k_row > kRows * g)) g = (1024 + strips - 1) / strips;
         if (layers > 1 && g < (k_max + kLong - 1) / kLong) g = (k_max + kLong - 1) / kLong;
         return {sc, 1, std::max(1, std::min(g, k_max / 32))};
     }
@@ -771,8 +786,8 @@ static BatchedShape batched_shape(int dtype, int n_out, int k_max, bool mc, int 
     return {kMWaveCols, kMWaves, g};
 }
 
-int batched_shares(int dtype, int n_out, int k_max, bool mc, int layers) {
-    return batched_shape(dtype, n_out, k_max, mc, layers).shares;
+int batched_shares(int dtype, int n_out, int k_max, int k_row, bool mc, int layers) {
+    return batched_shape(dtype, n_out, k_max, k_row, mc, layers).shares;
 }
 
 hipError_t launch_union(const UnionParams& p, int layers, hipStream_t stream) {
@@ -784,7 +799,7 @@ hipError_t launch_union(const UnionParams& p, int layers, hipStream_t stream) {
 
 hipError_t launch_batched_gemv(const BatchedGemvParams& p, int shares, bool mc, int layers, hipStream_t stream,
                                int pk) {
-    const BatchedShape shape = batched_shape(p.dtype, p.n_out, p.k_max, mc, layers);
+    const BatchedShape shape = batched_shape(p.dtype, p.n_out, p.k_max, p.k_max, mc, layers);   // (strip and kw)
     dim3 grid((p.n_out + shape.strip - 1) / shape.strip, shares, layers);
     if (layers < 1 || layers > kStackLayers) return hipErrorInvalidValue;
     if (layers == 1) return launch_product(one_layer(p), mc, shape.kw, grid, stream, pk);

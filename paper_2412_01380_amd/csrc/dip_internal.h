@@ -300,7 +300,8 @@ struct BatchedReduceParams {
     int64_t out_layer_stride;
 };
 bool batched_on_matrix_cores(int dtype, int batch, int64_t n_in, int64_t row_stride);
-int batched_shares(int dtype, int n_out, int k_max, bool mc, int layers);
+// (k_max: most listed columns, k_row: most columns a batch row selects)
+int batched_shares(int dtype, int n_out, int k_max, int k_row, bool mc, int layers);
 hipError_t launch_union(const UnionParams& p, int layers, hipStream_t stream);
 hipError_t launch_batched_gemv(const BatchedGemvParams& p, int shares, bool mc, int layers, hipStream_t stream,
                                int prof_kind);

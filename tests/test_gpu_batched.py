@@ -291,3 +291,32 @@ def test_batched_int4_matrix_core_rows_of_tiny_activations(D, B, scale_log2, lay
                 # (the matrix-core product's bar; that two columns trade places at the threshold of the second
                 # point because h is rounded otherwise has a chance of about d_ff * 2e-7, 1e-3 per row)
                 assert rel_l2(Yg[l, b], y) <= 2e-4, (l, b)
+
+
+@pytest.mark.parametrize("B", [1, 2])
+def test_batched_int4_sums_are_as_exact_as_the_one_row_call(D, B):
+    """Error of y against 64 bits through the batched call and through the one-row call: the offset of the
+    int4 codes grows with a share of the listed columns, so shares must not get longer than the
+    product of one layer can bear (a third longer: 1.27 to 1.35 times the one-row call's error).  The median
+    of 6 rows, each of 3072 outputs, whose error norms agree to a few percent."""
+    d, f, k_in, k_mid = 3072, 8192, 1690, 4506
+    w = layer_weights(d, f, seed=41, layer=0, dtype="int4")
+    mlp = D.Mlp(make_weight(D, w["ug"]), make_weight(D, w["d"]))
+    ws = workspace(max(D.dip_swiglu_mlp_forward_workspace_bytes(mlp, k_in, k_mid),
+                       D.dip_swiglu_mlp_forward_batched_workspace_bytes(mlp, B, k_in, k_mid)))
+    X = np.stack([ar1_laplace_stream(1, d, seed=950 + i)[0] for i in range(6)]).reshape(6 // B, B, d)
+    Xd, Y, Y1 = dev_f32(X), torch.empty(6, d, device="cuda"), torch.empty(6, d, device="cuda")
+    for i in range(6 // B):
+        D.dip_swiglu_mlp_forward_batched(mlp, Xd[i], B, k_in, k_mid, None, None, 0.2, Y[i * B:], None, None, None, ws)
+        for b in range(B):
+            D.dip_swiglu_mlp_forward(mlp, Xd[i, b], k_in, k_mid, None, None, 0.2, Y1[i * B + b], None, ws)
+    torch.cuda.synchronize()
+    errs = []
+    for i, x in enumerate(X.reshape(6, d)):
+        u = O.gathered_gemv(w["ug"], x, O.topk(O.score(x, None, 0.2), k_in)[1])
+        h = u[:f] * O.silu(u[f:])                        # 64 bits
+        idx2 = np.sort(np.argsort(-np.abs(h), kind="stable")[:k_mid])
+        y = h[idx2] @ O.widen_rows(w["d"], idx2)
+        errs.append([rel_l2(a[i].cpu().numpy(), y) for a in (Y, Y1)])
+    batched, single = np.median(np.array(errs), axis=0)
+    assert batched <= 1.2 * single, (batched, single)
