@@ -471,6 +471,12 @@ __global__ __launch_bounds__(kMWaves * 64, 2) void bgemv_q4_mfma_kernel(BatchedG
     const char* wbytes = static_cast<const char*>(p.layer[layer].w);
     const uint32_t row_stride = (uint32_t)p.row_stride;
     const int k = min((int)p.k_dev[layer], p.k_max);
+    // (asked for together with k: left to itself the compiler puts them into a round trip of their own)
+    uint32_t row_max[kMaxRows];
+#pragma unroll
+    for (int b = 0; b < kMaxRows; ++b) row_max[b] = rowmax[b];
+#pragma unroll
+    for (int b = 0; b < kMaxRows; ++b) asm volatile("" : : "s"(row_max[b]));
     const int share = ((k + G - 1) / G + kMRowSet - 1) / kMRowSet * kMRowSet;
     const int kb = min(k, g * share), ke = min(k, kb + share);
 
@@ -491,9 +497,10 @@ __global__ __launch_bounds__(kMWaves * 64, 2) void bgemv_q4_mfma_kernel(BatchedG
     const float m_scale = second ? 1024.0f : 1.0f;
     const float whole = second ? 1.0f : 0.0f;
     // the rows' powers of two, on their own: below maxima of 2^-114 they have no room for the 2^10
+    // (rows past the batch are staged, with whatever factor, and not read)
     float up[kMaxRows];
 #pragma unroll
-    for (int b = 0; b < kMaxRows; ++b) up[b] = row_scale_up(rowmax[min(b, B - 1)]);
+    for (int b = 0; b < kMaxRows; ++b) up[b] = row_scale_up(row_max[b]);
 
     struct Codes { u32x2 q[8]; };
     auto request = [&](int t, Codes& x) {
