@@ -496,12 +496,6 @@ __global__ __launch_bounds__(kMWaves * 64, 2) void bgemv_q4_mfma_kernel(BatchedG
     const bool second = c >= 8;
     const float m_scale = second ? 1024.0f : 1.0f;
     const float whole = second ? 1.0f : 0.0f;
-    // the rows' powers of two, on their own: below maxima of 2^-114 they have no room for the 2^10
-    // (rows past the batch are staged, with whatever factor, and not read)
-    float up[kMaxRows];
-#pragma unroll
-    for (int b = 0; b < kMaxRows; ++b) up[b] = row_scale_up(row_max[b]);
-
     struct Codes { u32x2 q[8]; };
     auto request = [&](int t, Codes& x) {
         const uint4 o0 = *reinterpret_cast<const uint4*>(&sh.st.off[t + 8 * r]);
@@ -571,6 +565,16 @@ __global__ __launch_bounds__(kMWaves * 64, 2) void bgemv_q4_mfma_kernel(BatchedG
                 row[j] = uidx[c0 + t];
 #pragma unroll
                 for (int b = 0; b < kMaxRows; ++b) m[j][b] = uval[min(b, B - 1) * p.list_layer_stride + c0 + t];
+            }
+            // The rows' powers of two, on their own (below maxima of 2^-114 they have no room for the 2^10) and
+            // not before the loads above are on their way, which is what the asm is for.  Rows past the
+            // batch are staged, with whatever factor, and not read.
+            float up[kMaxRows];
+#pragma unroll
+            for (int b = 0; b < kMaxRows; ++b) {
+                uint32_t bits = row_max[b];
+                asm volatile("" : "+s"(bits));
+                up[b] = row_scale_up(bits);
             }
 #pragma unroll
             for (int j = 0; j < R; ++j) {
