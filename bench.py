@@ -12,11 +12,16 @@ The default workload is BASELINE configs[3]: the Phi-3-Medium-shaped stack of 40
 keep ratio 0.3, DIP-CA with an LRU cache over half of the columns, gamma 0.2.  Steps walk the
 stack token-major; exactly --steps of them form a timed block, and the reported time is the
 median over --repeats repeats of that block (run back to back until a repeat lasts 20 ms).
+Every layer has an input stream of its own, so the layers of a token go to the library in one
+stack call, which runs layers that do not depend on each other phase by phase.  A decoder's MLP
+layers do depend on each other: the rate of one call per layer is reported beside the headline
+("one_call_per_layer").
 """
 from __future__ import annotations
 
 import argparse
 import json
+import math
 import os
 import sys
 import time
@@ -74,19 +79,19 @@ def parse():
     return ap.parse_args()
 
 
-def measured_traffic(workload: str, ratio: float, shape) -> "int | None":
-    """HBM bytes per up/gate launch from the committed rocprofv3 counter summaries
-    (FETCH_SIZE + WRITE_SIZE, each scaled by a plain copy of known size), if one was taken
-    for this workload and launch shape; otherwise None."""
+def measured_traffic(workload: str, ratio: float, kernel: str, layers: float) -> "int | None":
+    """HBM bytes per up/gate launch over `layers` layers from the committed rocprofv3 counter
+    summaries (FETCH_SIZE + WRITE_SIZE per layer, each scaled by a plain copy of known size), if
+    one was taken for this workload and kernel; otherwise None."""
     import glob
-    want = {"workload": workload, "ratio": f"{ratio:g}", "shape": ",".join(str(v) for v in shape)}
+    want = {"workload": workload, "ratio": f"{ratio:g}", "kernel": kernel}
     for path in sorted(glob.glob(os.path.join(ROOT, "profiles", "hbm_traffic_*.txt"))):
         for line in open(path):
             if not line.startswith("workload="):
                 continue
             kv = dict(tok.split("=", 1) for tok in line.split())
             if all(kv.get(k) == v for k, v in want.items()):
-                return int(kv["gemv_upgate_fetch_bytes"]) + int(kv["gemv_upgate_write_bytes"])
+                return int(layers * (int(kv["fetch_bytes_per_layer"]) + int(kv["write_bytes_per_layer"])))
     return None
 
 
@@ -380,7 +385,7 @@ def timed_repeats(one_block, blocks, repeats, min_repeat_ms):
         short = min(times) * 1e3
         if short >= min_repeat_ms:
             break
-        blocks = int(np.ceil(blocks * 1.15 * min_repeat_ms / max(short, 1e-3)))
+        blocks = math.ceil(blocks * 1.15 * min_repeat_ms / max(short, 1e-3))
     return blocks, times
 
 
@@ -548,7 +553,6 @@ def main():
     dn_bytes = bytes_of(k_mid * d)
     fused_ug = D.dip_fused_launch_shape(mlps[0].w_ug, k_in, bundled=True)
     fused_dn = D.dip_fused_launch_shape(mlps[0].w_d, k_mid, bundled=False)
-    launches = (1 if fused_ug else 2) + (1 if fused_dn else 2)
     out = {
         "metric": "DIP MLP decode tokens/s at batch 1 + achieved HBM GB/s vs peak on gathered bytes",
         "value": steps_per_s,
@@ -567,8 +571,7 @@ def main():
             "inputs": cfg.inputs, "weights_dtype": cfg.dtype,
             "weight_bytes_resident": int(L * bytes_of(3 * d * f)),
             "gathered_bytes_per_step": gathered,
-            "step": f"one token through one MLP layer ({launches} kernel launches"
-                    + (", cache updates of a token's layers batched into one more" if use_cache else "") + ")",
+            "step": "one token through one MLP layer",
             "batch": 1,
             "launch": launch_mode,
         },
@@ -595,6 +598,23 @@ def main():
         out["calibration_copy_bytes"] = {"read": int(src.numel() * 4), "written": int(dst.numel() * 4)}
         del src, dst
 
+    # ---- the same layer-steps, one call per layer ------------------------------------------
+    ws1 = torch.empty(D.dip_swiglu_mlp_forward_workspace_bytes(mlps[0], k_in, k_mid), dtype=torch.uint8, device="cuda")
+    at = [run.pos]
+
+    def layer_calls(n=4 * L):
+        for _ in range(n):
+            t, l = divmod(at[0], L)
+            D.dip_swiglu_mlp_forward(mlps[l], Xd[t % n_tok, l], k_in, k_mid, cins[l] if use_cache else None,
+                                     cmids[l] if use_cache else None, gamma, Yd[l], None, ws1)
+            at[0] += 1
+    layer_calls()
+    blocks1, times1 = timed_repeats(layer_calls, max(1, int(a.min_repeat_ms / (0.2 * L))), a.repeats, a.min_repeat_ms)
+    ms1 = statistics.median(times1) / (blocks1 * 4 * L) * 1e3
+    out["one_call_per_layer"] = {"ms_per_step": ms1, "tokens_per_s": 1e3 / ms1 / L if a.config != 2 else None,
+                                 "call": "dip_swiglu_mlp_forward"}
+    run.pos = at[0]
+
     # ---- per-kernel durations from HIP events bound to the dispatches ---------------------
     ceiling = None
     if not a.no_kernel_events:
@@ -607,7 +627,11 @@ def main():
         prof["cache_updates"] = D.dip_profile_read(7)
         D.dip_profile_disable()
         out["kernels_us"] = {k: (v[0] / v[1] * 1e3 if v[1] else None) for k, v in prof.items()}
-        out["launches_per_step"] = sum(v[1] for v in prof.values()) / n_prof
+        # (a stack call that runs phase by phase launches each product once for all of its layers, and a
+        #  reduction, without events, behind it)
+        phases = 0 < prof["gemv_upgate"][1] < n_prof
+        out["launches_per_step"] = (sum(v[1] for v in prof.values())
+                                    + (prof["gemv_upgate"][1] + prof["gemv_down"][1] if phases else 0)) / n_prof
         # a plain streaming read of 4 GiB in the same run: the ceiling a load-only kernel reaches here
         buf = torch.zeros(1 << 30, dtype=torch.int32, device="cuda")
         sink = torch.zeros(1, dtype=torch.int32, device="cuda")
@@ -623,30 +647,25 @@ def main():
         del buf
         shape_ug = fused_ug or D.dip_gemv_launch_shape(mlps[0].w_ug, k_in, bundled=True)
         shape_dn = fused_dn or D.dip_gemv_launch_shape(mlps[0].w_d, k_mid, bundled=False)
-        out["launch_shapes"] = {"gemv_upgate": list(shape_ug), "gemv_down": list(shape_dn),
+        out["launch_shapes"] = {"of": "one call per layer", "gemv_upgate": list(shape_ug), "gemv_down": list(shape_dn),
                                 "fields": "lanes_per_row, waves, ksplit, unroll",
                                 "selection_inside_the_product": [bool(fused_ug), bool(fused_dn)]}
-        ug_ms, ug_n = prof["gemv_upgate"]
-        dn_ms, dn_n = prof["gemv_down"]
-        if ug_n:
-            ach = ug_bytes / (ug_ms / ug_n * 1e-3) / 1e9
-            out["roofline"] = {"bound": "hbm", "achieved": ach, "peak": HBM_PEAK_GBS, "unit": "GB/s",
-                               "frac": ach / HBM_PEAK_GBS,
-                               "traffic": measured_traffic(cfg.name, r, shape_ug),
-                               "kernel": ("fused_kernel (scores + top-K + gathered up/gate + SwiGLU in one launch)"
-                                          if fused_ug else "gemv_kernel (up/gate + SwiGLU)"),
-                               "algorithmic_bytes_per_launch": ug_bytes,
-                               "avg_launch_us": ug_ms / ug_n * 1e3, "launches": ug_n,
-                               "ceiling_GBps": ceiling, "frac_of_ceiling": ach / ceiling}
-        if dn_n:
-            ach = dn_bytes / (dn_ms / dn_n * 1e-3) / 1e9
-            out["roofline_down"] = {"bound": "hbm", "achieved": ach, "peak": HBM_PEAK_GBS, "unit": "GB/s",
-                                    "frac": ach / HBM_PEAK_GBS,
-                                    "kernel": ("fused_kernel (scores + top-K + gathered down in one launch)"
-                                               if fused_dn else "gemv_kernel (down)"),
-                                    "algorithmic_bytes_per_launch": dn_bytes,
-                                    "avg_launch_us": dn_ms / dn_n * 1e3, "launches": dn_n,
-                                    "ceiling_GBps": ceiling, "frac_of_ceiling": ach / ceiling}
+        names = [("stack_product_kernel (gathered %s rows of several layers)" if phases else
+                  "fused_kernel (scores + top-K + gathered %s in one launch)" if fused else "gemv_kernel (%s)") % part
+                 for part, fused in (("up/gate", fused_ug), ("down", fused_dn))]
+        for key, name, nbytes, (ms, n) in (("roofline", names[0], ug_bytes, prof["gemv_upgate"]),
+                                           ("roofline_down", names[1], dn_bytes, prof["gemv_down"])):
+            if not n:
+                continue
+            layers = n_prof / n                  # a launch covers (on average) so many layer-steps
+            ach = nbytes * layers / (ms / n * 1e-3) / 1e9
+            out[key] = {"bound": "hbm", "achieved": ach, "peak": HBM_PEAK_GBS, "unit": "GB/s", "frac": ach / HBM_PEAK_GBS,
+                        "kernel": name, "layers_per_launch": layers,
+                        "algorithmic_bytes_per_launch": int(nbytes * layers),
+                        "avg_launch_us": ms / n * 1e3, "launches": n,
+                        "ceiling_GBps": ceiling, "frac_of_ceiling": ach / ceiling}
+            if key == "roofline":
+                out[key]["traffic"] = measured_traffic(cfg.name, r, name.split()[0], layers)
 
     # ---- eviction policies and the penalty, on fresh caches (Sec. 6.4), and what the measured hit
     #      rates mean on the paper's simulated phone (Sec. 6.1, App. A) --------------------------
@@ -788,15 +807,15 @@ def bench_batched(a, D, cfg, mlps, host0, X, Xd, cins, cmids, L, B, r, frac, gam
     D.dip_profile_disable()
     ug_ms, ug_n = prof["gemv_upgate"]
     dn_ms, dn_n = prof["gemv_down"]
-    ach = ug_bytes / (ug_ms / ug_n * 1e-3) / 1e9
+    ug_layers, dn_layers = n_prof / ug_n, n_prof / dn_n      # a launch covers (on average) so many layer-steps
 
     # Which roofline binds a batched product: HBM on the bytes of the union, or the plain vector
     # ALU on the arithmetic every stored code costs -- B multiply-adds (2 B flops) plus about 3
     # operations to unpack it -- against 157.3 TFLOP/s (256 compute units x 4 x 64-lane fp32 FMA
-    # per 4 cycles x 2.4 GHz).  From 3 rows on the multiply-adds of int4 weights run on the matrix
-    # cores, the unpacking stays on the vector ALU; the vector-ALU model is quoted for every B.
+    # per 4 cycles x 2.4 GHz).  From 3 rows on the multiply-adds run on the matrix cores and only the
+    # unpacking is left on the vector ALU.
     def two_bounds(n_cols, codes_per_col, nbytes, us):
-        ops = n_cols * codes_per_col * (2 * B + 3)
+        ops = n_cols * codes_per_col * (2 * B + 3 if B < 3 else 3)
         t_hbm, t_alu = nbytes / (HBM_PEAK_GBS * 1e9), ops / (VALU_PEAK_TFLOPS * 1e12)
         hbm = {"achieved_GBps": nbytes / (us * 1e-6) / 1e9, "peak_GBps": HBM_PEAK_GBS,
                "frac": nbytes / (us * 1e-6) / 1e9 / HBM_PEAK_GBS, "model_us": t_hbm * 1e6}
@@ -804,8 +823,8 @@ def bench_batched(a, D, cfg, mlps, host0, X, Xd, cins, cmids, L, B, r, frac, gam
                "frac": ops / (us * 1e-6) / 1e12 / VALU_PEAK_TFLOPS, "model_us": t_alu * 1e6, "ops_per_launch": ops}
         return ("alu" if t_alu > t_hbm else "hbm"), hbm, alu
     ug_us, dn_us = ug_ms / ug_n * 1e3, dn_ms / dn_n * 1e3
-    ug_bound, ug_hbm, ug_alu = two_bounds(u_in, 2 * f, ug_bytes, ug_us)
-    dn_bound, dn_hbm, dn_alu = two_bounds(u_mid, d, dn_bytes, dn_us)
+    ug_bound, ug_hbm, ug_alu = two_bounds(u_in * ug_layers, 2 * f, ug_bytes * ug_layers, ug_us)
+    dn_bound, dn_hbm, dn_alu = two_bounds(u_mid * dn_layers, d, dn_bytes * dn_layers, dn_us)
 
     def roof(bound, hbm, alu, **extra):
         o = ({"bound": "alu", "achieved": alu["achieved_TFLOPs"], "peak": VALU_PEAK_TFLOPS, "unit": "TFLOP/s",
@@ -840,10 +859,12 @@ def bench_batched(a, D, cfg, mlps, host0, X, Xd, cins, cmids, L, B, r, frac, gam
         "kernels_us": {k: (v[0] / v[1] * 1e3 if v[1] else None) for k, v in prof.items()},
         "roofline": roof(ug_bound, ug_hbm, ug_alu,
                          kernel="batched gathered product (up/gate), bytes and codes of the measured union",
-                         algorithmic_bytes_per_launch=ug_bytes, avg_launch_us=ug_us, launches=ug_n),
+                         layers_per_launch=ug_layers, algorithmic_bytes_per_launch=ug_bytes * ug_layers,
+                         avg_launch_us=ug_us, launches=ug_n),
         "roofline_down": roof(dn_bound, dn_hbm, dn_alu,
                               kernel="batched gathered product (down), bytes and codes of the measured union",
-                              algorithmic_bytes_per_launch=dn_bytes, avg_launch_us=dn_us, launches=dn_n),
+                              layers_per_launch=dn_layers, algorithmic_bytes_per_launch=dn_bytes * dn_layers,
+                              avg_launch_us=dn_us, launches=dn_n),
     }
     print(json.dumps(out))
 
