@@ -94,10 +94,9 @@ struct Q4 {
         const uint16_t b = (uint16_t)(v >> 16);
         return (float)__builtin_bit_cast(_Float16, b);
     }
-    // m24 = multiplier * up for codes in bits 0-3 of a half, m20 = multiplier * up / 16 for bits 4-7
+    // (odd codes are read 16 times as large as even ones, and their sums stay so until a span ends)
     template <int B>
-    __device__ static __forceinline__ void fma(const raw_t& q, const float (&m24)[B], const float (&m20)[B],
-                                               float (&acc)[B][16]) {
+    __device__ static __forceinline__ void fma(const raw_t& q, const float (&m)[B], float (&acc)[B][16]) {
 #pragma unroll
         for (int i = 0; i < 2; ++i) {
             const uint32_t o = q[i] ^ 0x88888888u, o8 = o >> 8;
@@ -106,14 +105,14 @@ struct Q4 {
 #pragma unroll
             for (int b = 0; b < B; ++b) {
                 float* a = acc[b] + 8 * i;
-                a[0] = fmaf(lo(c04), m24[b], a[0]);
-                a[4] = fmaf(hi(c04), m24[b], a[4]);
-                a[1] = fmaf(lo(c15), m20[b], a[1]);
-                a[5] = fmaf(hi(c15), m20[b], a[5]);
-                a[2] = fmaf(lo(c26), m24[b], a[2]);
-                a[6] = fmaf(hi(c26), m24[b], a[6]);
-                a[3] = fmaf(lo(c37), m20[b], a[3]);
-                a[7] = fmaf(hi(c37), m20[b], a[7]);
+                a[0] = fmaf(lo(c04), m[b], a[0]);
+                a[4] = fmaf(hi(c04), m[b], a[4]);
+                a[1] = fmaf(lo(c15), m[b], a[1]);
+                a[5] = fmaf(hi(c15), m[b], a[5]);
+                a[2] = fmaf(lo(c26), m[b], a[2]);
+                a[6] = fmaf(hi(c26), m[b], a[6]);
+                a[3] = fmaf(lo(c37), m[b], a[3]);
+                a[7] = fmaf(hi(c37), m[b], a[7]);
             }
         }
     }
@@ -199,38 +198,26 @@ __global__ __launch_bounds__(Shape<B>::kWaves * 64) void stack_product_kernel(St
             for (int u = 0; u < N; ++u) {
                 mult[u][b] = m[FIRST + u][b];
                 if constexpr (E::kScaled) {
-                    mult[u][b] *= (float)__builtin_bit_cast(_Float16, x.sc[FIRST + u]);
+                    mult[u][b] = fmaf(mult[u][b] * up[b], (float)__builtin_bit_cast(_Float16, x.sc[FIRST + u]), 0.0f);
                     sum += mult[u][b];
                 }
             }
             if constexpr (OPEN) {
-                float first = 0.f;
-                if constexpr (E::kScaled) first = sum * (up[b] * (-8.0f / 16777216.0f));
+                const float first = E::kScaled ? sum * (-8.0f / 16777216.0f) : 0.f;
 #pragma unroll
-                for (int e = 0; e < EPL; ++e) acc[b][e] = first;
+                for (int e = 0; e < EPL; ++e) acc[b][e] = E::kScaled && (e & 1) ? 16.0f * first : first;
             }
         }
 #pragma unroll
-        for (int u = 0; u < N; ++u) {
-            if constexpr (E::kScaled) {
-                float m24[B], m20[B];
-#pragma unroll
-                for (int b = 0; b < B; ++b) {
-                    m24[b] = mult[u][b] * up[b];
-                    m20[b] = mult[u][b] * (up[b] * 0.0625f);
-                }
-                E::template fma<B>(x.q[FIRST + u], m24, m20, acc);
-            } else {
-                E::template fma<B>(x.q[FIRST + u], mult[u], acc);
-            }
-        }
+        for (int u = 0; u < N; ++u) E::template fma<B>(x.q[FIRST + u], mult[u], acc);
     };
     // ... and ends in the totals
     auto close = [&] {
 #pragma unroll
         for (int b = 0; b < B; ++b)
 #pragma unroll
-            for (int e = 0; e < EPL; ++e) tot[b][e] += acc[b][e];
+            for (int e = 0; e < EPL; ++e)
+                tot[b][e] = E::kScaled && (e & 1) ? fmaf(acc[b][e], 0.0625f, tot[b][e]) : tot[b][e] + acc[b][e];
     };
     // block number POS after the start of a span
     auto multiply = [&](auto POS, const Pairs& b, const Rows& x) {
