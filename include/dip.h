@@ -280,9 +280,9 @@ int32_t dip_swiglu_mlp_forward(const dip_mlp* mlp, const float* x, int32_t k_in,
  * library load until the process ends.  The call allocates and frees nothing.  A layer
  * whose dip_swiglu_mlp_forward_workspace_bytes() exceeds DIP_STATIC_SCRATCH_BYTES is
  * rejected with DIP_ERR_WORKSPACE and nothing is enqueued.  All calls on one GPU share that
- * GPU's array (it keeps the previous call's contents; what must start at zero is cleared by
- * the call's own kernels): calls that overlap on one GPU -- different streams, or replays
- * of graphs that contain it running concurrently -- race.
+ * GPU's array, which may hold anything when a call starts (a launch knows its own ticket
+ * counts by their tag; nothing is cleared): calls that overlap on one GPU -- different streams,
+ * or replays of graphs that contain it running concurrently -- race.
  */
 #define DIP_STATIC_SCRATCH_BYTES (4u << 20)
 int32_t dip_swiglu_mlp_forward_noalloc(const dip_mlp* mlp, const float* x, int32_t k_in, int32_t k_mid,
@@ -298,8 +298,13 @@ int32_t dip_swiglu_mlp_forward_noalloc(const dip_mlp* mlp, const float* x, int32
  * input of a later one or the output of another, they run one after the other, in order.
  * mlps / caches_in / caches_mid are host arrays of n_layers descriptors; the cache arrays
  * may be NULL (DIP).  Every layer and pruning point needs a dip_cache of its own (the call
- * rejects shared state): all caches are scored in their layers' launches and updated
- * together in one launch at the end of the call.
+ * rejects shared state): every cache is scored with its state from before the call and all
+ * are updated together in one launch at the end of it.
+ * Results are those of one dip_swiglu_mlp_forward per layer up to the rounding of the fp32 sums:
+ * the order of a sum follows from the shape, k and the number of consecutive layers of one
+ * shape, so it is the same for every call like this one, and another for a call per layer, over
+ * part of the stack, or with rows that overlap.  Where two scores of point 2 agree to within
+ * that rounding the masks, and with them the caches, may differ by that pair of columns.
  * ws: dip_swiglu_mlp_forward_stack_workspace_bytes() bytes, 256-aligned.
  */
 size_t dip_swiglu_mlp_forward_stack_workspace_bytes(const dip_mlp* mlps, int32_t n_layers,
@@ -341,9 +346,10 @@ int32_t dip_swiglu_mlp_forward_batched(const dip_mlp* mlp, const float* X, int32
 /*
  * The batched forward for n_layers independent layers in one call: layer l reads its `batch`
  * rows at X + l * x_stride ([batch][d_model], contiguous) and writes Y + l * y_stride (strides
- * in floats), with k_in[l] / k_mid[l] kept per row (host arrays).  Cache rules as in
- * dip_swiglu_mlp_forward_stack: one dip_cache per layer and point, all updated -- once each,
- * with the union of the layer's row masks -- in one launch at the end of the call.
+ * in floats), with k_in[l] / k_mid[l] kept per row (host arrays).  Rules for overlapping rows,
+ * for the order of the sums and for caches as in dip_swiglu_mlp_forward_stack: one dip_cache per
+ * layer and point, all updated -- once each, with the union of the layer's row masks -- in one
+ * launch at the end of the call.
  */
 size_t dip_swiglu_mlp_forward_batched_stack_workspace_bytes(const dip_mlp* mlps, int32_t n_layers, int32_t batch,
                                                             const int32_t* k_in /* host */,
