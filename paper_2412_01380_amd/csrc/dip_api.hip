@@ -259,7 +259,7 @@ int32_t forward_one(const dip_mlp* mlp, const ForwardPlan& pl, const float* x, i
 // products, the reductions, the selections of point 2, the down products and reductions.  A
 // layer on its own is two launches that each wait for a selection and end with a reduction;
 // over a stack those waits are paid once per call.
-// Measured per layer-step: Phi-3-Medium shape, bf16, 40 layers 45.3 us layer by layer, 27.7 us in phases.
+// Measured per layer-step: Phi-3-Medium shape, bf16, 40 layers 46.0 us layer by layer, 27.6 us in phases.
 // Shorter stacks keep the launches of a call per layer, and with them its bits (phases would take
 // 24 us for two or three layers of 512 x 1536 in bf16 where those take 31 and 45, 78 and 106 us of
 // 5120 x 17920 where they take 91 and 136).
@@ -815,7 +815,7 @@ namespace {
 // The union masks go to `uwords` (two per layer) and the cache updates with them are left to the
 // caller (one launch at the end of the call).  The stage outputs (nullable) take layers == 1.
 // Measured per layer-step over 40 layers of the Phi-3-Medium shape with int4 weights: layer by
-// layer 62.8 us at two rows and 83.8 us at eight, in phases 14.2 and 21.4 us.
+// layer 62.8 us at two rows and 83.8 us at eight, in phases 14.5 and 20.4 us.
 int32_t batched_group(const dip_mlp* mlps, int layers, const float* X, int64_t x_stride, int batch, const int32_t* k_in,
                       const int32_t* k_mid, int k_stride, const dip_cache* caches_in, const dip_cache* caches_mid,
                       float gamma, float* Y, int64_t y_stride, uint32_t* mask_in_out, float* h_out,

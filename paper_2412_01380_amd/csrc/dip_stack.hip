@@ -19,7 +19,7 @@
 // Rounding: sums of short spans of rows are added to the totals, wavefronts and shares in pairs.  In
 // one chain per wavefront the error against 64 bits was up to 3 times that of a layer on its own
 // (40 layers of the Phi-3-Medium shape: bf16 1.2, at 8 rows 1.6, int4 2.1, at 2 rows 3.1 times); in
-// spans it is 0.75 to 1.0 times, for 3 to 5 % more time with int4 rows and none with the others.
+// spans it is 0.75 to 1.0 times, for 1 to 7 % more time with int4 rows and none with the others.
 //
 // A small batch reads the union of its rows' lists with one multiplier per batch row, which stay
 // scalar; the row of weights is widened once for all of them.
