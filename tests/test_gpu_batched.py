@@ -320,3 +320,26 @@ def test_batched_int4_sums_are_as_exact_as_the_one_row_call(D, B):
         errs.append([rel_l2(a[i].cpu().numpy(), y) for a in (Y, Y1)])
     batched, single = np.median(np.array(errs), axis=0)
     assert batched <= 1.2 * single, (batched, single)
+
+
+@pytest.mark.parametrize("layers", [2, 3])
+@pytest.mark.parametrize("B", [1, 2])
+def test_batched_int4_stack_of_two_and_three_layers(D, B, layers):
+    """int4 batches of one and two rows run in the kernel of the stacks from two layers on: k at the edges of
+    its blocks of 4 and 8 rows and of its shares of 64, against one call per layer."""
+    d, f = 640, 1408
+    w = layer_weights(d, f, seed=42, layer=0, dtype="int4")
+    mlp = D.Mlp(make_weight(D, w["ug"]), make_weight(D, w["d"]))
+    stack = D.MlpStack([mlp] * layers)
+    Xd = dev_f32(np.stack([ar1_laplace_stream(1, d, seed=970 + i)[0] for i in range(layers * B)]).reshape(layers, B, d))
+    Y, Y1 = torch.empty(layers, B, d, device="cuda"), torch.empty(layers, B, d, device="cuda")
+    for k_in, k_mid in ((1, 3), (4, 5), (31, 33), (63, 64), (65, 129), (257, 700), (d, f)):
+        ws = workspace(D.dip_swiglu_mlp_forward_batched_stack_workspace_bytes(stack, B, k_in, k_mid))
+        ws.fill_(0xFF)        # nothing is expected of the workspace's contents
+        D.dip_swiglu_mlp_forward_batched_stack(stack, Xd, B * d, B, k_in, k_mid, 0.2, Y, B * d, ws)
+        one = workspace(D.dip_swiglu_mlp_forward_batched_workspace_bytes(mlp, B, k_in, k_mid))
+        for l in range(layers):
+            D.dip_swiglu_mlp_forward_batched(mlp, Xd[l], B, k_in, k_mid, None, None, 0.2, Y1[l], None, None, None, one)
+        torch.cuda.synchronize()
+        # the order of the fp32 sums, with int4's offset in them: a few 1e-7 each way
+        assert rel_l2(Y.cpu().numpy(), Y1.cpu().numpy()) <= 4e-6, (k_in, k_mid)
